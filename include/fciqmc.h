@@ -316,11 +316,14 @@ fq_status fq_stage_times(const fq_ctx *ctx, double *ms7);
 
 /* Per-kernel device time of the last fq_step call (timing on), summed over its
  * iterations, one slot per launch of an iteration in launch order: begin,
- * attempt partition, spawn, sort histogram, sort passes 0..7,
+ * attempt partition, spawn, CCMC clusters, sort histogram, sort passes 0..7,
  * reduce, collision fix-up, reduce (repeat), projection gather, projection,
- * projection check, merge partition, merge, new-determinant diagonals, end.
- * *n_slots receives the slot count (22) and
- * *n_iterations the number of timed iterations. */
+ * projection check, merge partition, merge, new-determinant diagonals, CCMC
+ * pairs, end. A slot whose work another launch does or the iteration does not
+ * need (the histogram, fix-up and repeat slots; sort passes beyond the one to
+ * four an iteration makes) holds the empty interval between two events.
+ * *n_slots receives the slot count (24) and *n_iterations the number of timed
+ * iterations. */
 fq_status fq_kernel_times(const fq_ctx *ctx, double *ms, int32_t cap, int32_t *n_slots,
                           int64_t *n_iterations);
 

@@ -346,7 +346,9 @@ __global__ __launch_bounds__(CC_T) void k_ccmc_clusters(Work w)
         for (int x = 0; x < 2; ++x) {
             if (!has[x]) continue;
             const long long o = (long long)wbase + (x == 0 ? r0i : r1i);
-            w.sp.skey[o] = make_skey(hash64<W>(rkey[x]) & w.hmask, 0u, w.rb);
+            const uint64_t sk = make_skey(hash64<W>(rkey[x]) & w.hmask, 0u, w.rb);
+            w.sp.skey[o] = sk;
+            for (int q = 0; q < w.sort_p; ++q) atomicAdd(&c->hist[7 - q][(sk >> (56 - 8 * q)) & 255], 1u);
             uint64_t *rec = w.sp.rec + (size_t)o * (W + 1);
 #pragma unroll
             for (int q = 0; q < W; ++q) rec[q] = rkey[x][q];

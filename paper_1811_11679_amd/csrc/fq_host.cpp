@@ -228,8 +228,8 @@ size_t table_bytes(const HostSys &s)
 
 struct Layout {
     size_t total = 0;
-    size_t ctl, acc, hist, shift, rep, sys, tables, att, span, mpart, st_scan, st_sort, st_red, st_merge, st_att;
-    size_t part_red, part_mrg, newdet, bpart;
+    size_t ctl, acc, hist, shift, rep, sys, tables, att, span, mpart, st_scan, st_sort, st_merge, st_att;
+    size_t part_red, part_mrg, newdet;
     size_t main[2][6];
     size_t sp[7];
     size_t u[4];
@@ -290,10 +290,8 @@ Layout make_layout(int R, int W, int64_t mcap, int64_t scap, int64_t tables, int
     L.span = take(8 * (size_t)(span_capacity(mcap, scap, W) + 2));
     L.mpart = take(8 * (size_t)(tiles_of(mcap + scap, 512) + 2));
     L.newdet = take((size_t)mcap + 16);
-    L.bpart = take(sizeof(BoundaryPart) * (size_t)tiles_of(scap, 1024));
     L.st_scan = take(8 * (size_t)tiles_of(mcap, 2048));
     L.st_sort = take(8 * 256 * (size_t)tiles_of(scap, SORT_TILE_MIN));
-    L.st_red = take(8 * (size_t)tiles_of(scap, 1024));
     L.st_merge = take(8 * (size_t)tiles_of(mcap + scap, 512));
     L.st_att = take(8 * (size_t)tiles_of(mcap + scap, 512));
     L.part_red = take(8 * (size_t)PART_MAX_BLOCKS * acc_rows(R) * EST_FIELDS);
@@ -363,6 +361,7 @@ struct fq_ctx {
     int cur = 0;
     int64_t main_cap = 0, spawn_cap = 0;
     Grids grids{};
+    int64_t spawn_hint = 0;  // spawned records an iteration is expected to write (the last one's count)
     std::vector<double> shift;
     std::vector<int> vary;
     std::vector<int64_t> nprev;
@@ -500,6 +499,33 @@ void drop_graphs(fq_ctx *c)
     }
 }
 
+// Radix passes for n spawned records: enough top digits that a group of equal
+// digits holds at most 32 records on average, which the collapse ranks by
+// counting (measured: a pass costs 8..15 us on a small list and 90 us at 7e6
+// records; without the third pass the collapse of 6e6 records took 545 us).
+// The replica id takes rb of the digits' bits and one replica may hold nearly
+// all records, so those bits do not count.
+int passes_for(int64_t n, int rb)
+{
+    int p = 1;
+    while (p < SORT_P_MAX && (8 * p <= rb || n > (int64_t(32) << (8 * p - rb)))) ++p;
+    return p;
+}
+
+// The plan of the next block of iterations. Any plan gives the same lists; a
+// larger one than needed is kept until the records are four times too few, so
+// that captured graphs last.
+void choose_plan(fq_ctx *c)
+{
+    const int64_t n = c->spawn_hint + c->spawn_hint / 2;
+    int p = passes_for(n, c->rb);
+    if (p < c->w.sort_p) p = std::min(c->w.sort_p, passes_for(4 * n, c->rb));
+    if (p != c->w.sort_p) {
+        c->w.sort_p = p;
+        drop_graphs(c);
+    }
+}
+
 struct HostEntry {
     uint64_t skey;
     uint64_t key[MAXW];
@@ -580,6 +606,7 @@ fq_status upload_main(fq_ctx *c, const std::vector<HostEntry> &e)
     ctl.n_main_new = n;
     HIPCHK(c, h2d(c->stream, c->w.ctl, &ctl, sizeof(Ctl)));
     HIPCHK(c, hipStreamSynchronize(c->stream));
+    c->spawn_hint = std::min<int64_t>(ctl.n_att_new / 4, c->spawn_cap);  // a fraction of the attempts spawns
     return FQ_OK;
 }
 
@@ -886,10 +913,8 @@ fq_status init_system(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc, con
     w.span_lo = (long long *)(c->ws + c->L.span);
     w.mpart = (long long *)(c->ws + c->L.mpart);
     w.newdet = (uint8_t *)(c->ws + c->L.newdet);
-    w.bpart = (BoundaryPart *)(c->ws + c->L.bpart);
     w.st_scan = (unsigned long long *)(c->ws + c->L.st_scan);
     w.st_sort = (unsigned long long *)(c->ws + c->L.st_sort);
-    w.st_red = (unsigned long long *)(c->ws + c->L.st_red);
     w.st_merge = (unsigned long long *)(c->ws + c->L.st_merge);
     w.st_att = (unsigned long long *)(c->ws + c->L.st_att);
     w.part_red = (long long *)(c->ws + c->L.part_red);
@@ -928,6 +953,7 @@ fq_status init_system(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc, con
     w.R = c->R;
     w.rb = c->rb;
     w.hmask = c->hmask;
+    w.sort_p = 1;
     w.tau_search = c->qmc[0].tau_search;
     w.dm = dm_method(c->method) ? c->method : 0;
     w.ccmc_trunc = c->method == FQ_CCMC ? c->qmc[0].ccmc_truncation : 0;
@@ -1077,8 +1103,6 @@ fq_status init_system(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc, con
             w.lds_tables = (int32_t)bytes;
         }
     }
-    c->grids.hist = ncu * 4;
-    c->grids.fixup = ncu * 2;
     c->grids.det = ncu * 4;
     c->grids.newdiag = ncu * 8;
 
@@ -1221,6 +1245,7 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
             if (c->L.single_key > c->L.st_ccmc)
                 HIPCHK(c, fill0(c->stream, c->ws + c->L.st_ccmc, c->L.single_key - c->L.st_ccmc));
         }
+        choose_plan(c);
         const int64_t t0 = c->t;
         const int cur0 = c->cur;
         const int nb = (int)(stop - t0);
@@ -1342,6 +1367,7 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
             if (err & ERR_SPAWN_CAP) return fail(c, FQ_ECAPACITY, "spawn capacity exceeded");
             return fail(c, FQ_ECAPACITY, "main list capacity exceeded");
         }
+        c->spawn_hint = (int64_t)ctl.n_spawn;
         fold_spawn_ratio(c, t0 + 1, stop);
         for (int64_t it = t0 + 1; it <= stop; ++it) {
             for (int r = 0; r < c->R; ++r) {
@@ -1593,8 +1619,10 @@ fq_status fq_export_spawns(const fq_ctx *cc, int32_t instance, uint64_t *keys, i
     std::vector<int32_t> am(n);
     std::vector<uint8_t> in(n);
     if (n) {
-        HIPCHK(c, d2h(c->stream, sk.data(), c->w.sp.skey, 8 * n));
-        HIPCHK(c, d2h(c->stream, ix.data(), c->w.sp.idx, 4 * n));
+        // the buffer the last radix pass wrote
+        const bool odd = (c->w.sort_p & 1) != 0;
+        HIPCHK(c, d2h(c->stream, sk.data(), odd ? c->w.sp.skey2 : c->w.sp.skey, 8 * n));
+        HIPCHK(c, d2h(c->stream, ix.data(), odd ? c->w.sp.idx2 : c->w.sp.idx, 4 * n));
         std::vector<uint64_t> rec((size_t)n * (c->W + 1));
         HIPCHK(c, d2h(c->stream, rec.data(), c->w.sp.rec, 8 * rec.size()));
         for (int64_t j = 0; j < n; ++j) {

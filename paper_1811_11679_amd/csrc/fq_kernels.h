@@ -34,8 +34,6 @@ enum : uint32_t {
 enum : int {
     TK_SCAN = 0,
     TK_SORT = 1,   // 8 passes: 1..8
-    TK_RED1 = 9,
-    TK_RED2 = 10,
     TK_MERGE = 11,
     TK_SPAWN = 12,
     TK_CCMC = 13,
@@ -48,10 +46,10 @@ struct Ctl {
     long long n_att;       // total spawning attempts this iteration
     long long n_att_new;   // attempts of the list the merge has just written
     unsigned long long n_spawn;  // spawned walkers written
-    long long n_uniq;      // distinct spawned determinants
+    long long pad_uniq;
     uint32_t t;            // iteration counter (1 = first iteration)
     uint32_t err;
-    uint32_t collision;    // equal sort keys with different determinants seen
+    uint32_t pad_coll;
     uint32_t ss_active;
     uint32_t pad_ts;
     uint32_t tickets[TK_COUNT];
@@ -89,6 +87,8 @@ constexpr int ACC_LDS_R = 64;
 // chosen per context (the host sizes the per-tile digit status words for the
 // smallest tile)
 constexpr int SORT_TILE_MIN = 2048;
+// radix passes the plan may use
+constexpr int SORT_P_MAX = 4;
 
 // spawn tiles: SP_T threads of SI attempts each (2, 4 or 8 for keys of up to
 // two words, chosen per context; 2 for longer keys, whose children take more
@@ -140,6 +140,9 @@ struct SpawnList {
     uint32_t *idx2;
 };
 
+// Distinct spawned determinants, sorted, one place per spawned record: places
+// beyond a tile's determinants repeat its last one and are marked in flag.
+constexpr uint32_t UNIQ_INITIATOR = 1u, UNIQ_FILLER = 2u;
 struct UniqList {
     uint64_t *skey;
     uint64_t *key;  // word-major
@@ -169,17 +172,6 @@ struct DetSpace {
     const uint64_t *key_sorted;   // [W][R*n]
 };
 
-// The part of a spawned-list segment that lies in one reduction tile when the
-// segment's head is in an earlier tile (at most one per tile): added to the
-// segment's total after the reduction.
-struct BoundaryPart {
-    long long sum;
-    long long seg;
-    uint32_t flag;
-    uint32_t valid;
-    long long pad;
-};
-
 struct Work {
     Ctl *ctl;
     EstAcc *acc;        // [R]
@@ -191,8 +183,7 @@ struct Work {
     long long *span_lo;    // [spans + 1]
     long long *mpart;      // merge partition [tiles + 1]
     uint8_t *newdet;       // [main_cap]: 1 where the merge wrote a new determinant (K_jj still to compute)
-    BoundaryPart *bpart;   // [reduction tiles]
-    unsigned long long *st_scan, *st_sort, *st_red, *st_merge, *st_att;  // look-back status
+    unsigned long long *st_scan, *st_sort, *st_merge, *st_att;  // look-back status
     // per-block estimator partials of the reduction and the merge:
     // [block][acc_rows(R)][EST_FIELDS], folded into acc by the epilogue
     long long *part_red, *part_mrg;
@@ -202,6 +193,8 @@ struct Work {
     DetSpace ds;
     long long main_cap, spawn_cap, span_cap;
     int32_t R, rb, W, hist_len;
+    int32_t sort_p;  // radix passes over the top digits of the sort keys (1..SORT_P_MAX)
+    int32_t pad_sort;
     uint64_t hmask;  // hash bits that enter a sort key (all but in collision tests)
     int32_t tau_search;  // track the maxima of the time-step search (per replica)
     int32_t lds_tables;  // bytes of UEG tables the spawn kernel stages in LDS (0: read from global)
@@ -222,7 +215,7 @@ struct Work {
 
 // launch geometry of the persistent kernels
 struct Grids {
-    int scan, part, spawn, hist, sort, reduce, fixup, merge, det;
+    int scan, part, spawn, sort, reduce, merge, det;
     int spawn_lds;  // dynamic LDS bytes of the spawn kernel
     int newdiag;    // blocks of the new-determinant diagonal kernel
     // tile shapes (compile-time variants chosen at run time; results do not
@@ -242,6 +235,9 @@ hipError_t enqueue_iteration(const Work &w, int kind, const Grids &g, hipStream_
 // spawn kernel), 1 = singles-pair estimator of the new list (after the
 // merge), 2 = the same for the current list (set-up)
 hipError_t enqueue_ccmc(int stage, int kind, const Work &w, const Grids &g, hipStream_t s);
+// segmented reduction of the spawned list after `passes` radix passes
+hipError_t enqueue_collapse(const Work &w, const Grids &g, int passes, hipStream_t s);
+int collapse_occupancy();
 // set-up work: 0 = H_00 of every system, 1 = K_ii - H_00, attempt counts and
 // attempt offsets of the current list of n entries, 2 = K_DD of the
 // deterministic space

@@ -31,19 +31,6 @@ struct LocalAcc {
     }
 };
 
-__device__ __forceinline__ void acc_table_clear(long long *tab, int rl)
-{
-    for (int i = threadIdx.x; i < rl * EST_FIELDS; i += blockDim.x) tab[i] = 0;
-}
-
-__device__ __forceinline__ void acc_add(long long *tab, int rl, EstAcc *g, int rep, int f, long long v)
-{
-    if (rep < rl)
-        atomicAdd((unsigned long long *)&tab[rep * EST_FIELDS + f], (unsigned long long)v);
-    else
-        atomicAdd((unsigned long long *)(&g[rep].nw + f), (unsigned long long)v);
-}
-
 // the thread's values to the block table, lane by lane
 __device__ __forceinline__ void acc_spill(LocalAcc &a, long long *tab, int rl, EstAcc *g)
 {
@@ -87,8 +74,6 @@ __device__ void acc_finish(LocalAcc &a, bool active, long long *tab, int rl, Est
     for (int i = threadIdx.x; i < rl * EST_FIELDS; i += blockDim.x) part[(size_t)i * PART_MAX_BLOCKS + blockIdx.x] = tab[i];
 }
 
-enum { F_NW = 0, F_NOCC, F_N0, F_NSPAWN, F_NUNIQ, F_FLIPS, F_REJU, F_DEATH, F_SPAWN, F_REJ, F_L0, F_L1, F_L2, F_L3 };
-
 // Time-step search maxima, per replica, into the replica's estimator record
 // of the iteration: KD = false the largest |H_ji| / p_gen (as its bits), true
 // the largest K_ii (as an order-preserving key). A thread keeps the running
@@ -131,9 +116,7 @@ __global__ void k_begin(Work w)
         c->t += 1;
         c->n_main = c->n_main_new;
         c->n_spawn = 0;
-        c->n_uniq = 0;
         c->n_att = c->n_att_new;
-        c->collision = 0;
         c->ccmc_n0 = 0;
         c->ccmc_nex = 0;
         c->n_single = 0;
@@ -286,6 +269,8 @@ __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
     __shared__ uint64_t s_rkey[W][SP_STAGE];
     __shared__ int32_t s_ramp[SP_STAGE];
     __shared__ uint8_t s_rinit[SP_STAGE];
+    __shared__ uint32_t s_hist[SORT_P_MAX][256];  // digits of the block's sort keys, for the radix passes
+    for (int i = threadIdx.x; i < w.sort_p * 256; i += SP_T) (&s_hist[0][0])[i] = 0;
     const long long total = c->n_att;
     const long long nspans = (total + SPAN - 1) / SPAN;
     if (nspans + 1 > w.span_cap) return;
@@ -596,7 +581,9 @@ __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
                 uint64_t key[W];
 #pragma unroll
                 for (int q = 0; q < W; ++q) key[q] = s_rkey[q][p];
-                w.sp.skey[o] = make_skey(hash64<W>(key) & w.hmask, MULTI ? s_rrep[p] : 0u, w.rb);
+                const uint64_t sk = make_skey(hash64<W>(key) & w.hmask, MULTI ? s_rrep[p] : 0u, w.rb);
+                w.sp.skey[o] = sk;
+                for (int q = 0; q < w.sort_p; ++q) atomicAdd(&s_hist[q][(sk >> (56 - 8 * q)) & 255], 1u);
                 uint64_t *rec = w.sp.rec + (size_t)o * (W + 1);
 #pragma unroll
                 for (int q = 0; q < W; ++q) rec[q] = key[q];
@@ -606,7 +593,9 @@ __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
             for (int it = 0; it < SP_I; ++it)
                 if (has[it] && rk[it] >= SP_STAGE) {
                     const long long o = base + rk[it];
-                    w.sp.skey[o] = make_skey(hash64<W>(child[it]) & w.hmask, rep[it], w.rb);
+                    const uint64_t sk = make_skey(hash64<W>(child[it]) & w.hmask, rep[it], w.rb);
+                    w.sp.skey[o] = sk;
+                    for (int q = 0; q < w.sort_p; ++q) atomicAdd(&s_hist[q][(sk >> (56 - 8 * q)) & 255], 1u);
                     uint64_t *rec = w.sp.rec + (size_t)o * (W + 1);
 #pragma unroll
                     for (int q = 0; q < W; ++q) rec[q] = child[it][q];
@@ -616,35 +605,20 @@ __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
         __syncthreads();
     }
     if (ts) ts_finish<false>(w, rs_max, rs_rep, rs_max > 0.0);
+    for (int i = threadIdx.x; i < w.sort_p * 256; i += SP_T) {
+        const uint32_t v = (&s_hist[0][0])[i];
+        if (v) atomicAdd(&c->hist[7 - (i >> 8)][i & 255], v);
+    }
 }
 
 // ---------------------------------------------------------------------------
-// onesweep LSD radix sort of (sort key, index) pairs, 8 passes of 8 bits
+// onesweep LSD radix passes of (sort key, index) pairs over the top digits of
+// 8 bits (Work::sort_p of them)
 // ---------------------------------------------------------------------------
 // Tiles of 256 threads x OS_I keys: 2048 (8 per thread), 3072 (12: three
 // blocks fit a compute unit's LDS) or 4096 (16), chosen per context
 constexpr int OS_T = 256, OS_WAVES = OS_T / 64;
 static_assert(SORT_TILE_MIN == 8 * OS_T, "the status words are sized for the smallest sort tile");
-
-__global__ __launch_bounds__(256) void k_sort_hist(Work w)
-{
-    Ctl *c = w.ctl;
-    if (c->err) return;
-    __shared__ uint32_t h[8][256];
-    for (int i = threadIdx.x; i < 8 * 256; i += blockDim.x) (&h[0][0])[i] = 0;
-    __syncthreads();
-    const long long n = (long long)min(c->n_spawn, (unsigned long long)w.spawn_cap);
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        const uint64_t k = w.sp.skey[i];
-#pragma unroll
-        for (int p = 0; p < 8; ++p) atomicAdd(&h[p][(k >> (8 * p)) & 255], 1u);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < 8 * 256; i += blockDim.x) {
-        const uint32_t v = (&h[0][0])[i];
-        if (v) atomicAdd(&(&c->hist[0][0])[i], v);
-    }
-}
 
 // predecessors a digit's look-back reads per round trip after the first (an
 // instrumented copy measured ~12 round trips per walk at four; eight made
@@ -795,426 +769,6 @@ __global__ __launch_bounds__(OS_T) void k_sort_pass(Work w, int pass, const uint
 }
 
 // ---------------------------------------------------------------------------
-// segmented reduction of the sorted spawned list (Sec. 2.4 annihilation:
-// combine walkers on the same determinant): one entry per distinct
-// determinant with the int64 sum of amplitudes and the OR of initiator flags
-// ---------------------------------------------------------------------------
-constexpr int RD_T = 256, RD_I = 4, RD_TILE = RD_T * RD_I;
-
-template <int W>
-__global__ __launch_bounds__(RD_T) void k_reduce(Work w, int second)
-{
-    Ctl *c = w.ctl;
-    if (c->err) return;
-    if (second && !c->collision) return;
-    extern __shared__ __align__(16) unsigned char dyn_lds[];
-    long long *tab = (long long *)dyn_lds;  // estimator table, acc_rows(R) rows
-    const int rl = acc_rows(w.R);
-    acc_table_clear(tab, rl);
-    __shared__ uint64_t s_lastk[RD_T][W];
-    __shared__ uint64_t s_lasts[RD_T];
-    __shared__ long long s_tile, s_base;
-    __shared__ long long s_red[8];
-    __shared__ long long s_ws[RD_T / 64];
-    __shared__ uint32_t s_wf[RD_T / 64];
-    __shared__ int s_wr[RD_T / 64];
-    const long long n = (long long)min(c->n_spawn, (unsigned long long)w.spawn_cap);
-    const long long ntiles = (n + RD_TILE - 1) / RD_TILE;
-    const uint32_t epoch = epoch_of(c->t, second ? 10 : 9);
-    const uint64_t *skey = w.sp.skey;
-    const uint32_t *idx = w.sp.idx;
-    LocalAcc acc;
-    acc.clear();
-    acc.rep = -1;
-    bool any = false;
-    for (;;) {
-        if (threadIdx.x == 0) s_tile = atomicAdd(&c->tickets[second ? TK_RED2 : TK_RED1], 1u);
-        __syncthreads();
-        const long long tile = s_tile;
-        if (tile >= ntiles) break;
-        const long long base = tile * RD_TILE + (long long)threadIdx.x * RD_I;
-        uint64_t sk[RD_I], kk[RD_I][W];
-        int32_t am[RD_I];
-        uint32_t fl[RD_I];
-        bool valid[RD_I];
-        bool head[RD_I];
-        int nh = 0;
-        // first pass with keys of up to two words: the tile's count goes out
-        // before the gathers (below); otherwise after them
-        constexpr bool SHORT = W <= 2;
-        const bool early = SHORT && !second;
-        long long ex = 0, tot = 0;
-        if constexpr (SHORT) {
-#pragma unroll
-            for (int i = 0; i < RD_I; ++i) {
-                const long long e = base + i;
-                valid[i] = e < n;
-                sk[i] = valid[i] ? skey[e] : 0;
-            }
-            s_lasts[threadIdx.x] = sk[RD_I - 1];
-            __syncthreads();
-            const uint64_t psk0 = threadIdx.x > 0 ? s_lasts[threadIdx.x - 1] : (base > 0 ? skey[base - 1] : 0);
-            // First pass, keys of up to two words: a segment starts wherever the
-            // sort key changes (equal keys holding different determinants are a
-            // collision, flagged below, after which the fix-up and the second pass
-            // redo the tile). The tile's segment count then needs no record, so it
-            // is published before the gathers, and the tiles after this one do not
-            // wait on them. (Longer keys keep the single look-back after the
-            // gathers: the early count would cost them a wave per SIMD.)
-            if (early) {
-                int nh0 = 0;
-                uint64_t p = psk0;
-                bool hp = base > 0;
-#pragma unroll
-                for (int i = 0; i < RD_I; ++i) {
-                    if (valid[i]) nh0 += (hp && p == sk[i]) ? 0 : 1;
-                    p = sk[i];
-                    hp = true;
-                }
-                ex = block_excl_scan<long long>((long long)nh0, tot, s_red);
-                if (threadIdx.x == 0) lookback_publish(w.st_red, tile, epoch, tot);
-            }
-#pragma unroll
-            for (int i = 0; i < RD_I; ++i) {
-                am[i] = 0;
-                fl[i] = 0;
-#pragma unroll
-                for (int q = 0; q < W; ++q) kk[i][q] = 0;
-                if (valid[i]) {
-                    const uint64_t *rec = w.sp.rec + (size_t)idx[base + i] * (W + 1);
-#pragma unroll
-                    for (int q = 0; q < W; ++q) kk[i][q] = rec[q];
-                    const uint64_t ai = rec[W];
-                    am[i] = (int32_t)(uint32_t)ai;
-                    fl[i] = (uint32_t)(ai >> 32);
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < W; ++q) s_lastk[threadIdx.x][q] = kk[RD_I - 1][q];
-            __syncthreads();
-            uint64_t psk = psk0;
-            uint64_t pk[W];
-            bool have_prev = base > 0;
-            if (threadIdx.x > 0) {
-#pragma unroll
-                for (int q = 0; q < W; ++q) pk[q] = s_lastk[threadIdx.x - 1][q];
-            } else if (base > 0) {
-                const uint64_t *rec = w.sp.rec + (size_t)idx[base - 1] * (W + 1);
-#pragma unroll
-                for (int q = 0; q < W; ++q) pk[q] = rec[q];
-            } else {
-#pragma unroll
-                for (int q = 0; q < W; ++q) pk[q] = 0;
-            }
-#pragma unroll
-            for (int i = 0; i < RD_I; ++i) {
-                head[i] = false;
-                if (valid[i]) {
-                    const bool same_s = have_prev && psk == sk[i];
-                    const bool same_k = same_s && key_eq<W>(pk, kk[i]);
-                    if (same_s && !same_k) atomicOr(&c->collision, 1u);
-                    // the second pass follows the key order the fix-up gave each
-                    // collision run
-                    head[i] = early ? !same_s : !same_k;
-                    nh += head[i];
-                }
-                psk = sk[i];
-#pragma unroll
-                for (int q = 0; q < W; ++q) pk[q] = kk[i][q];
-                have_prev = true;
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < RD_I; ++i) {
-                const long long e = base + i;
-                valid[i] = e < n;
-                sk[i] = 0;
-                am[i] = 0;
-                fl[i] = 0;
-#pragma unroll
-                for (int q = 0; q < W; ++q) kk[i][q] = 0;
-                if (valid[i]) {
-                    sk[i] = skey[e];
-                    const uint64_t *rec = w.sp.rec + (size_t)idx[e] * (W + 1);
-#pragma unroll
-                    for (int q = 0; q < W; ++q) kk[i][q] = rec[q];
-                    const uint64_t ai = rec[W];
-                    am[i] = (int32_t)(uint32_t)ai;
-                    fl[i] = (uint32_t)(ai >> 32);
-                }
-            }
-            s_lasts[threadIdx.x] = sk[RD_I - 1];
-#pragma unroll
-            for (int q = 0; q < W; ++q) s_lastk[threadIdx.x][q] = kk[RD_I - 1][q];
-            __syncthreads();
-            uint64_t psk;
-            uint64_t pk[W];
-            bool have_prev = base > 0;
-            if (threadIdx.x > 0) {
-                psk = s_lasts[threadIdx.x - 1];
-#pragma unroll
-                for (int q = 0; q < W; ++q) pk[q] = s_lastk[threadIdx.x - 1][q];
-            } else if (base > 0) {
-                psk = skey[base - 1];
-                const uint64_t *rec = w.sp.rec + (size_t)idx[base - 1] * (W + 1);
-#pragma unroll
-                for (int q = 0; q < W; ++q) pk[q] = rec[q];
-            } else {
-                psk = 0;
-#pragma unroll
-                for (int q = 0; q < W; ++q) pk[q] = 0;
-            }
-#pragma unroll
-            for (int i = 0; i < RD_I; ++i) {
-                head[i] = false;
-                if (valid[i]) {
-                    const bool same_s = have_prev && psk == sk[i];
-                    const bool same_k = same_s && key_eq<W>(pk, kk[i]);
-                    if (same_s && !same_k) atomicOr(&c->collision, 1u);
-                    head[i] = !same_k;
-                    nh += head[i];
-                }
-                psk = sk[i];
-#pragma unroll
-                for (int q = 0; q < W; ++q) pk[q] = kk[i][q];
-                have_prev = true;
-            }
-        }
-        // the open segment at this thread's end (after its last head, or all
-        // of its elements without a head), passed to the right
-        long long lead_s = 0, tail_s = 0;
-        uint32_t lead_f = 0, tail_f = 0;
-        {
-            bool seen = false;
-#pragma unroll
-            for (int i = 0; i < RD_I; ++i) {
-                if (!valid[i]) continue;
-                if (head[i]) {
-                    seen = true;
-                    tail_s = 0;
-                    tail_f = 0;
-                }
-                if (seen) {
-                    tail_s += am[i];
-                    tail_f |= fl[i];
-                } else {
-                    lead_s += am[i];
-                    lead_f |= fl[i];
-                }
-            }
-        }
-        // exclusive segmented scan over the tile's threads: the partial sum and
-        // flags of the segment open at this thread's first element (threads
-        // with a head restart it)
-        long long carry_s;
-        uint32_t carry_f;
-        {
-            const int lane = lane_id(), wid = threadIdx.x >> 6;
-            bool r = nh > 0;
-            long long xs = r ? tail_s : lead_s;
-            uint32_t xf = r ? tail_f : lead_f;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const long long ys = __shfl_up(xs, o, 64);
-                const uint32_t yf = __shfl_up(xf, o, 64);
-                const bool yr = __shfl_up((int)r, o, 64) != 0;
-                if (lane >= o && !r) {
-                    xs += ys;
-                    xf |= yf;
-                    r = yr;
-                }
-            }
-            // wave totals, then the prefix of the earlier waves
-            if (lane == 63) {
-                s_ws[wid] = xs;
-                s_wf[wid] = xf;
-                s_wr[wid] = r ? 1 : 0;
-            }
-            long long es = __shfl_up(xs, 1, 64);
-            uint32_t ef = __shfl_up(xf, 1, 64);
-            bool er = __shfl_up((int)r, 1, 64) != 0;
-            if (lane == 0) {
-                es = 0;
-                ef = 0;
-                er = false;
-            }
-            __syncthreads();
-            if (!er) {
-                long long ps = 0;
-                uint32_t pf = 0;
-                for (int q = 0; q < wid; ++q) {
-                    if (s_wr[q]) {
-                        ps = 0;
-                        pf = 0;
-                    }
-                    ps += s_ws[q];
-                    pf |= s_wf[q];
-                }
-                es += ps;
-                ef |= pf;
-            }
-            carry_s = es;
-            carry_f = ef;
-        }
-        if (!early) ex = block_excl_scan<long long>((long long)nh, tot, s_red);
-        if (threadIdx.x < 64) {
-            const long long lb_ = early ? lookback_wait(w.st_red, tile, epoch, tot) : lookback(w.st_red, tile, epoch, tot);
-            if (threadIdx.x == 0) s_base = lb_;
-        }
-        __syncthreads();
-        // Segment totals. A segment is stored by the thread holding its last
-        // element in the tile: the thread of the next head, or the thread of
-        // the tile's last element. The part of a segment whose head lies in an
-        // earlier tile becomes this tile's boundary part.
-        const long long tile_end = min(tile * RD_TILE + RD_TILE, n);
-        long long seg = s_base + ex - 1;  // segment open at this thread's first element
-        long long run_s = carry_s;
-        uint32_t run_f = carry_f;
-        bool run_here = ex > 0;  // its head is in this tile
-        // whether the open segment holds elements of this tile before this thread
-        bool run_nonempty = threadIdx.x > 0;
-        BoundaryPart bp;
-        bp.sum = 0;
-        bp.seg = 0;
-        bp.flag = 0;
-        bp.valid = 0;
-        bp.pad = 0;
-        bool bp_mine = false;
-        if (threadIdx.x == 0 && valid[0] && head[0]) bp_mine = true;  // no boundary part: record it as such
-#pragma unroll
-        for (int i = 0; i < RD_I; ++i) {
-            if (!valid[i]) continue;
-            if (head[i]) {
-                if (run_nonempty) {
-                    if (run_here) {
-                        w.u.sum[seg] = run_s;
-                        w.u.flag[seg] = run_f;
-                    } else {
-                        bp.sum = run_s;
-                        bp.flag = run_f;
-                        bp.seg = s_base - 1;
-                        bp.valid = 1;
-                        bp_mine = true;
-                    }
-                }
-                ++seg;
-                w.u.skey[seg] = sk[i];
-#pragma unroll
-                for (int q = 0; q < W; ++q) w.u.key[(size_t)q * w.spawn_cap + seg] = kk[i][q];
-                run_s = 0;
-                run_f = 0;
-                run_here = true;
-            }
-            run_s += am[i];
-            run_f |= fl[i];
-            run_nonempty = true;
-            if (base + i == tile_end - 1) {
-                // the tile's last element closes its open segment here
-                if (run_here) {
-                    w.u.sum[seg] = run_s;
-                    w.u.flag[seg] = run_f;
-                } else {
-                    bp.sum = run_s;
-                    bp.flag = run_f;
-                    bp.seg = s_base - 1;
-                    bp.valid = 1;
-                    bp_mine = true;
-                }
-            }
-            acc_switch(acc, (int)skey_rep(sk[i], w.rb), tab, rl, w.acc);
-            acc.v[F_NSPAWN] += 1;
-            acc.v[F_SPAWN] += am[i];
-            acc.v[F_NUNIQ] += head[i] ? 1 : 0;
-            any = true;
-        }
-        if (bp_mine) w.bpart[tile] = bp;
-        if (tile == ntiles - 1 && threadIdx.x == 0) c->n_uniq = s_base + tot;
-        __syncthreads();
-    }
-    acc_finish(acc, any && acc.rep >= 0, tab, rl, w.acc, w.part_red);
-}
-
-// Rare path: equal sort keys holding different determinants (hash
-// collisions) are put in key order and the reduction is redone. A run of
-// equal sort keys can be long, since a determinant may receive many spawns:
-// it is only reordered when it holds more than one determinant, by moving the
-// entries of its smallest remaining determinant to the front, one determinant
-// at a time (stable; run length x distinct determinants gathers, through the
-// radix sort's ping-pong index buffer, which is free at this point).
-constexpr int FIXUP_MAX_KEYS = 64;
-
-template <int W>
-__device__ __forceinline__ void rec_key(const Work &w, uint32_t j, uint64_t (&k)[W])
-{
-#pragma unroll
-    for (int q = 0; q < W; ++q) k[q] = w.sp.rec[(size_t)j * (W + 1) + q];
-}
-
-template <int W>
-__global__ void k_fixup(Work w)
-{
-    Ctl *c = w.ctl;
-    if (c->err || !c->collision) return;
-    const long long n = (long long)min(c->n_spawn, (unsigned long long)w.spawn_cap);
-    const uint64_t *skey = w.sp.skey;
-    uint32_t *idx = w.sp.idx;
-    uint32_t *tmp = w.sp.idx2;
-    const long long gs = (long long)gridDim.x * blockDim.x;
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < w.R * (int)(sizeof(EstAcc) / 8); i += blockDim.x) {
-            const int r = i / (int)(sizeof(EstAcc) / 8), f = i % (int)(sizeof(EstAcc) / 8);
-            if (f == F_NSPAWN || f == F_NUNIQ || f == F_SPAWN) ((long long *)&w.acc[r])[f] = 0;
-        }
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gs) {
-        if (i > 0 && skey[i - 1] == skey[i]) continue;
-        uint64_t k0[W];
-        rec_key<W>(w, idx[i], k0);
-        long long e = i + 1;
-        bool mixed = false;
-        while (e < n && skey[e] == skey[i]) {
-            if (!mixed) {
-                uint64_t ke[W];
-                rec_key<W>(w, idx[e], ke);
-                mixed = !key_eq<W>(ke, k0);
-            }
-            ++e;
-        }
-        if (!mixed) continue;
-        for (long long a = i; a < e; ++a) tmp[a] = idx[a];
-        long long pos = i;
-        uint64_t prev[W];
-        for (int d = 0;; ++d) {
-            // the smallest determinant of the run above the last one placed
-            bool found = false;
-            uint64_t best[W];
-            for (long long a = i; a < e; ++a) {
-                uint64_t ka[W];
-                rec_key<W>(w, tmp[a], ka);
-                if (d > 0 && key_cmp<W>(ka, prev) <= 0) continue;
-                if (!found || key_cmp<W>(ka, best) < 0) {
-#pragma unroll
-                    for (int q = 0; q < W; ++q) best[q] = ka[q];
-                    found = true;
-                }
-            }
-            if (!found) break;
-            if (d == FIXUP_MAX_KEYS) {
-                // this many determinants on one sort key cannot come from hash collisions
-                atomicOr(&c->err, ERR_COLLISION);
-                break;
-            }
-            for (long long a = i; a < e; ++a) {
-                uint64_t ka[W];
-                rec_key<W>(w, tmp[a], ka);
-                if (key_eq<W>(ka, best)) idx[pos++] = tmp[a];
-            }
-#pragma unroll
-            for (int q = 0; q < W; ++q) prev[q] = best[q];
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // annihilation merge (Sec. 2.4; appendix "Parallelization"): merge-path merge
 // of the distinct spawned determinants into the sorted main list, fused with
 // death/cloning of existing entries, the deterministic-space update, the
@@ -1276,21 +830,8 @@ __global__ void k_merge_partition(Work w)
 {
     const Ctl *c = w.ctl;
     if (c->err) return;
-    {
-        // the segmented reduction's boundary parts (one per reduction tile at
-        // most): the last reduction launch of the iteration has finished
-        const long long ns = (long long)min(c->n_spawn, (unsigned long long)w.spawn_cap);
-        const long long nrt = (ns + RD_TILE - 1) / RD_TILE;
-        for (long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x; t < nrt; t += (long long)gridDim.x * blockDim.x) {
-            const BoundaryPart b = w.bpart[t];
-            if (b.valid) {
-                atomicAdd((unsigned long long *)&w.u.sum[b.seg], (unsigned long long)b.sum);
-                if (b.flag) atomicOr(&w.u.flag[b.seg], b.flag);
-            }
-        }
-    }
     constexpr int TILE = MergeCfg<W, MI>::TILE;
-    const long long na = c->n_main, nb = c->n_uniq;
+    const long long na = c->n_main, nb = (long long)min(c->n_spawn, (unsigned long long)w.spawn_cap);
     const long long ntiles = (na + nb + TILE - 1) / TILE;
     for (long long tile = (long long)blockIdx.x * blockDim.x + threadIdx.x; tile <= ntiles;
          tile += (long long)gridDim.x * blockDim.x) {
@@ -1398,7 +939,7 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T)) void k_merge(Work w)
     __shared__ int s_pa_ok, s_nb_ok;
     __shared__ long long s_tile, s_base, s_abase;
     __shared__ long long s_red[16];
-    const long long na = c->n_main, nb = c->n_uniq;
+    const long long na = c->n_main, nb = (long long)min(c->n_spawn, (unsigned long long)w.spawn_cap);
     const long long ntiles = (na + nb + TILE - 1) / TILE;
     const uint32_t t = c->t;
     const uint32_t epoch = epoch_of(t, 11), epoch_att = epoch_of(t, 13);
@@ -1560,7 +1101,7 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T)) void k_merge(Work w)
                 }
                 s_src[m] = (uint16_t)slot;
                 s_keep[m] = 0;
-                if (!matched) {
+                if (!matched && !(s_meta[slot] & (int32_t)UNIQ_FILLER)) {
                     const long long sum = s_val[slot];
                     const int32_t fl = s_meta[slot];
                     const int rep = MULTI ? (int)skey_rep(s_sk[slot], w.rb) : 0;
@@ -2064,14 +1605,10 @@ FQ_INSTT(K_UEG, 8, 2)
 FQ_INSTS(K_HUBBARD | K_PAIR, 2, 4)
 FQ_INSTS(K_UEG | K_PAIR, 2, 4)
 FQ_INSTS(K_MOLECULAR | K_PAIR, 2, 4)
-#define FQ_INSTW(W)                                        \
-    template __global__ void k_reduce<W>(Work, int);       \
-    template __global__ void k_fixup<W>(Work);             \
-    template __global__ void k_merge_partition<W, 2>(Work);
-FQ_INSTW(1)
-FQ_INSTW(2)
-FQ_INSTW(4)
-FQ_INSTW(8)
+template __global__ void k_merge_partition<1, 2>(Work);
+template __global__ void k_merge_partition<2, 2>(Work);
+template __global__ void k_merge_partition<4, 2>(Work);
+template __global__ void k_merge_partition<8, 2>(Work);
 template __global__ void k_merge_partition<1, 1>(Work);
 template __global__ void k_merge_partition<1, 4>(Work);
 template __global__ void k_merge_partition<2, 1>(Work);
@@ -2217,27 +1754,27 @@ static void launch_kind(const Work &w, const Grids &g, hipStream_t s, hipEvent_t
     rec();
     if (w.ccmc_trunc > 0) (void)enqueue_ccmc(0, KIND, w, g, s);
     rec();
-    k_sort_hist<<<g.hist, 256, 0, s>>>(w);
+    // (the digit histograms come with the spawned records)
     rec();
+    // the top digits of the sort key, lowest first; the collapse orders the rest
     uint64_t *K[2] = {w.sp.skey, w.sp.skey2};
     uint32_t *I[2] = {w.sp.idx, w.sp.idx2};
-    for (int p = 0; p < 8; ++p) {
-        const uint64_t *ki = K[p & 1];
-        const uint32_t *ii = p == 0 ? nullptr : I[p & 1];
+    for (int p = 8 - w.sort_p, q = 0; p < 8; ++p, ++q) {
+        const uint64_t *ki = K[q & 1];
+        const uint32_t *ii = q == 0 ? nullptr : I[q & 1];
         if (g.sort_i == 8)
-            k_sort_pass<8><<<g.sort, OS_T, 0, s>>>(w, p, ki, ii, K[(p + 1) & 1], I[(p + 1) & 1]);
+            k_sort_pass<8><<<g.sort, OS_T, 0, s>>>(w, p, ki, ii, K[(q + 1) & 1], I[(q + 1) & 1]);
         else if (g.sort_i == 16)
-            k_sort_pass<16><<<g.sort, OS_T, 0, s>>>(w, p, ki, ii, K[(p + 1) & 1], I[(p + 1) & 1]);
+            k_sort_pass<16><<<g.sort, OS_T, 0, s>>>(w, p, ki, ii, K[(q + 1) & 1], I[(q + 1) & 1]);
         else
-            k_sort_pass<12><<<g.sort, OS_T, 0, s>>>(w, p, ki, ii, K[(p + 1) & 1], I[(p + 1) & 1]);
+            k_sort_pass<12><<<g.sort, OS_T, 0, s>>>(w, p, ki, ii, K[(q + 1) & 1], I[(q + 1) & 1]);
         rec();
     }
+    for (int q = w.sort_p; q < 8; ++q) rec();  // unused timing slots
     const int accb = acc_rows(w.R) * EST_FIELDS * 8;
-    k_reduce<W><<<g.reduce, RD_T, accb, s>>>(w, 0);
+    (void)enqueue_collapse(w, g, w.sort_p, s);
     rec();
-    k_fixup<W><<<g.fixup, 256, 0, s>>>(w);
     rec();
-    k_reduce<W><<<g.reduce, RD_T, accb, s>>>(w, 1);
     rec();
     k_det_gather<<<g.det, 256, 0, s>>>(w);
     rec();
@@ -2331,7 +1868,7 @@ int occupancy_blocks(int which)
     case 0: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sort_pass<12>, OS_T, 0); break;
     case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_merge<K_UEG, 2, false, 2>, MergeCfg<2, 2>::T, 0); break;
     case 5: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_merge<K_UEG, 8, false, 2>, MergeCfg<8, 2>::T, 0); break;
-    case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_reduce<2>, RD_T, 0); break;
+    case 2: return collapse_occupancy();
     case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_scan_attempts, SCAN_T, 0); break;
     case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_spawn<K_UEG, 2, false, true, 4>, SP_T, 8192); break;
     default: break;

@@ -190,4 +190,23 @@ __device__ __forceinline__ void add_limbs4(long long &a0, long long &a1, long lo
     a3 += neg ? -l3 : l3;
 }
 
+// ---------------------------------------------------------------------------
+// estimator fields of a block's table in LDS (replicas below acc_rows(R); the
+// others are added to global memory directly)
+// ---------------------------------------------------------------------------
+enum { F_NW = 0, F_NOCC, F_N0, F_NSPAWN, F_NUNIQ, F_FLIPS, F_REJU, F_DEATH, F_SPAWN, F_REJ, F_L0, F_L1, F_L2, F_L3 };
+
+__device__ __forceinline__ void acc_table_clear(long long *tab, int rl)
+{
+    for (int i = threadIdx.x; i < rl * EST_FIELDS; i += blockDim.x) tab[i] = 0;
+}
+
+__device__ __forceinline__ void acc_add(long long *tab, int rl, EstAcc *g, int rep, int f, long long v)
+{
+    if (rep < rl)
+        atomicAdd((unsigned long long *)&tab[rep * EST_FIELDS + f], (unsigned long long)v);
+    else
+        atomicAdd((unsigned long long *)(&g[rep].nw + f), (unsigned long long)v);
+}
+
 }  // namespace fq

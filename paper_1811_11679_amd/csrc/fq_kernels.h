@@ -235,6 +235,12 @@ hipError_t enqueue_iteration(const Work &w, int kind, const Grids &g, hipStream_
 // spawn kernel), 1 = singles-pair estimator of the new list (after the
 // merge), 2 = the same for the current list (set-up)
 hipError_t enqueue_ccmc(int stage, int kind, const Work &w, const Grids &g, hipStream_t s);
+// spawning: part 0 the attempt partition, 1 the spawn
+hipError_t enqueue_spawn(int part, int kind, const Work &w, const Grids &g, hipStream_t s);
+int spawn_occupancy();
+// merge: part 0 the merge partition, 1 the merge, 2 the diagonal elements of the new determinants
+hipError_t enqueue_merge(int part, int kind, const Work &w, const Grids &g, hipStream_t s);
+int merge_occupancy(bool wide);
 // segmented reduction of the spawned list after `passes` radix passes
 hipError_t enqueue_collapse(const Work &w, const Grids &g, int passes, hipStream_t s);
 int collapse_occupancy();

@@ -209,4 +209,73 @@ __device__ __forceinline__ void acc_add(long long *tab, int rl, EstAcc *g, int r
         atomicAdd((unsigned long long *)(&g[rep].nw + f), (unsigned long long)v);
 }
 
+// Time-step search maxima, per replica, into the replica's estimator record
+// of the iteration: KD = false the largest |H_ji| / p_gen (as its bits), true
+// the largest K_ii (as an order-preserving key). A thread keeps the running
+// maximum of one replica and hands it over when it moves to another replica
+// and at the end of the kernel; there the wave reduces first when its holders
+// share one replica (the lists are sorted by replica, so they nearly always do).
+template <bool KD>
+__device__ __forceinline__ void ts_put(const Work &w, int rep, double v)
+{
+    if constexpr (KD)
+        atomicMax(&w.acc[rep].kd_key, ordered_key(v));
+    else
+        atomicMax(&w.acc[rep].rs_bits, (unsigned long long)__double_as_longlong(v));
+}
+
+template <bool KD>
+__device__ void ts_finish(const Work &w, double v, int rep, bool has)
+{
+    const uint64_t act = __ballot(has);
+    if (!act) return;
+    const int leader = __ffsll((unsigned long long)act) - 1;
+    const int r0 = __shfl(rep, leader, 64);
+    if (__ballot(has && rep != r0) == 0) {
+        const double m = wave_max(has ? v : -INFINITY);
+        if (lane_id() == leader) ts_put<KD>(w, r0, m);
+    } else if (has) {
+        ts_put<KD>(w, rep, v);
+    }
+}
+
+// The diagonal element death uses, relative to H_00: K_ii for a determinant;
+// for a pair (i, j) of the density-matrix methods (Sec. 2.3) (K_ii + K_jj) / 2
+// (DMQMC, the symmetrised Bloch equation) or K_jj - K_ii (IP-DMQMC, with H^0
+// the diagonal part of H).
+template <int KIND, int W>
+__device__ double entry_kdiag(const Work &w, const DevSys &sy, const uint64_t (&key)[W])
+{
+    if constexpr (is_pair(KIND)) {
+        constexpr int BK = base_kind(KIND), WH = W / 2;
+        uint64_t a[WH], b[WH];
+#pragma unroll
+        for (int x = 0; x < WH; ++x) {
+            a[x] = key[x];
+            b[x] = key[WH + x];
+        }
+        const double ki = diag_element<BK, WH>(sy, a) - sy.H00;
+        const double kj = diag_element<BK, WH>(sy, b) - sy.H00;
+        return w.dm == 1 ? (ki + kj) * 0.5 : kj - ki;
+    } else {
+        return diag_element<KIND, W>(sy, key) - sy.H00;
+    }
+}
+
+// calls fn<KIND, W> for the kernel kind and key width of a context
+#define FQ_DISPATCH(fn, ...)                                                                  \
+    switch (kind * 16 + w.W) {                                                               \
+    case K_HUBBARD * 16 + 1: fn<K_HUBBARD, 1>(__VA_ARGS__); break;                           \
+    case K_UEG * 16 + 1: fn<K_UEG, 1>(__VA_ARGS__); break;                                   \
+    case K_UEG * 16 + 2: fn<K_UEG, 2>(__VA_ARGS__); break;                                   \
+    case K_UEG * 16 + 4: fn<K_UEG, 4>(__VA_ARGS__); break;                                   \
+    case K_UEG * 16 + 8: fn<K_UEG, 8>(__VA_ARGS__); break;                                   \
+    case K_MOLECULAR * 16 + 1: fn<K_MOLECULAR, 1>(__VA_ARGS__); break;                       \
+    case K_MOLECULAR * 16 + 2: fn<K_MOLECULAR, 2>(__VA_ARGS__); break;                       \
+    case (K_HUBBARD | K_PAIR) * 16 + 2: fn<K_HUBBARD | K_PAIR, 2>(__VA_ARGS__); break;       \
+    case (K_UEG | K_PAIR) * 16 + 2: fn<K_UEG | K_PAIR, 2>(__VA_ARGS__); break;               \
+    case (K_MOLECULAR | K_PAIR) * 16 + 2: fn<K_MOLECULAR | K_PAIR, 2>(__VA_ARGS__); break;   \
+    default: return hipErrorInvalidValue;                                                    \
+    }
+
 }  // namespace fq

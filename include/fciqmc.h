@@ -355,17 +355,18 @@ fq_status fq_set_sort_key_bits(fq_ctx *ctx, int32_t bits);
 
 /* Launch geometry of the persistent kernels, in blocks: [0] spawn, [1] merge,
  * [2] radix-sort pass, [3] segmented reduction, [4] new-determinant
- * diagonals. A value <= 0 keeps the current one. Results do not depend on
+ * diagonals. A launch uses at most that many, and fewer where the lists have
+ * fewer tiles. A value <= 0 keeps the current one. Results do not depend on
  * the geometry (work is taken by ticket or grid stride); only speed does. */
 fq_status fq_set_launch(fq_ctx *ctx, const int32_t *blocks, int32_t n);
 fq_status fq_get_launch(const fq_ctx *ctx, int32_t *blocks, int32_t n);
 
 /* Tile shapes of the persistent kernels, among variants compiled into the
  * library: [0] spawning attempts per thread (2, 4 or 8; tiles of 256 threads),
- * [1] merge positions per thread (1, 2 or 4; tiles of 512 threads), [2]
+ * [1] merge positions per thread (1, 2 or 4; tiles of 256 threads), [2]
  * radix-sort keys per thread (8, 12 or 16; tiles of 256 threads). [0] and [1]
  * apply to determinant keys of one or two words (longer keys and pair keys
- * use 2 and 2, resp. 4 and 2); [2] to every context. Defaults 4, 2, 12. A value
+ * use 2 and 2, resp. 4 and 2); [2] to every context. Defaults 4, 4, 12. A value
  * <= 0 keeps the current one; any other value outside the list is FQ_EINVAL
  * (nothing changes). Results do not depend on the shapes (tiles only
  * partition the work; every prefix crossing tiles is exact); only speed does.

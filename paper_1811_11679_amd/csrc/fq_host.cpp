@@ -288,12 +288,12 @@ Layout make_layout(int R, int W, int64_t mcap, int64_t scap, int64_t tables, int
     L.tables = take((size_t)tables);
     L.att = take(8 * (size_t)(mcap + 1));
     L.span = take(8 * (size_t)(span_capacity(mcap, scap, W) + 2));
-    L.mpart = take(8 * (size_t)(tiles_of(mcap + scap, 512) + 2));
+    L.mpart = take(8 * (size_t)(tiles_of(mcap + scap, MERGE_TILE_MIN) + 2));
     L.newdet = take((size_t)mcap + 16);
     L.st_scan = take(8 * (size_t)tiles_of(mcap, 2048));
     L.st_sort = take(8 * 256 * (size_t)tiles_of(scap, SORT_TILE_MIN));
-    L.st_merge = take(8 * (size_t)tiles_of(mcap + scap, 512));
-    L.st_att = take(8 * (size_t)tiles_of(mcap + scap, 512));
+    L.st_merge = take(8 * (size_t)tiles_of(mcap + scap, MERGE_TILE_MIN));
+    L.st_att = take(8 * (size_t)tiles_of(mcap + scap, MERGE_TILE_MIN));
     L.part_red = take(8 * (size_t)PART_MAX_BLOCKS * acc_rows(R) * EST_FIELDS);
     L.part_mrg = take(8 * (size_t)PART_MAX_BLOCKS * acc_rows(R) * EST_FIELDS);
     for (int b = 0; b < 2; ++b) {
@@ -361,7 +361,9 @@ struct fq_ctx {
     int cur = 0;
     int64_t main_cap = 0, spawn_cap = 0;
     Grids grids{};
-    int64_t spawn_hint = 0;  // spawned records an iteration is expected to write (the last one's count)
+    // sizes the next iteration is expected to have (those of the last one)
+    int64_t spawn_hint = 0, main_hint = 0, att_hint = 0;
+    Grids plan{};  // launch geometry of the blocks being enqueued (choose_plan)
     std::vector<double> shift;
     std::vector<int> vary;
     std::vector<int64_t> nprev;
@@ -512,18 +514,47 @@ int passes_for(int64_t n, int rb)
     return p;
 }
 
-// The plan of the next block of iterations. Any plan gives the same lists; a
-// larger one than needed is kept until the records are four times too few, so
-// that captured graphs last.
+// The plan of the next block of iterations: radix passes and launch geometry
+// for the sizes the last block ended with. Any plan gives the same lists (the
+// kernels take their tiles by ticket or stride and read their sizes on the
+// device); blocks without a tile only cost their start: at 4e3 determinants
+// the kernels of an iteration took 165 us at the full grids. A plan is kept
+// until it is too small or several times too large, so captured graphs last.
+Grids sized_grids(const fq_ctx *c, double room)
+{
+    Grids g = c->grids;
+    auto fit = [&](int cap, int64_t units, int64_t per_block) {
+        const int64_t n = (int64_t)((double)((units + per_block - 1) / per_block) * room) + 4;
+        return (int)std::max<int64_t>(1, std::min<int64_t>(cap, n));
+    };
+    const int64_t ns = c->spawn_hint, nm = c->main_hint + c->spawn_hint;
+    g.part = fit(c->grids.part, std::max(c->att_hint / SPAN_MIN, nm / MERGE_TILE_MIN), 256);
+    g.spawn = fit(c->grids.spawn, c->att_hint, SP_T * (c->W <= 2 ? c->grids.spawn_i : 2));
+    g.sort = fit(c->grids.sort, ns, 256 * c->grids.sort_i);
+    g.reduce = fit(c->grids.reduce, ns, 768);
+    g.merge = fit(c->grids.merge, nm, MERGE_TILE_MIN * (c->W <= 2 ? c->grids.merge_i : 2));
+    g.newdiag = fit(c->grids.newdiag, nm, 16384);
+    g.ss = c->ss_active ? 1 : 0;
+    return g;
+}
+
 void choose_plan(fq_ctx *c)
 {
     const int64_t n = c->spawn_hint + c->spawn_hint / 2;
     int p = passes_for(n, c->rb);
     if (p < c->w.sort_p) p = std::min(c->w.sort_p, passes_for(4 * n, c->rb));
-    if (p != c->w.sort_p) {
-        c->w.sort_p = p;
-        drop_graphs(c);
-    }
+    const Grids lo = sized_grids(c, 1.0), hi = sized_grids(c, 8.0);
+    auto within = [](int x, int a, int b) { return x >= a && x <= b; };
+    const Grids &g = c->plan;
+    const bool keep = p == c->w.sort_p && g.ss == lo.ss && within(g.part, lo.part, hi.part) &&
+                      within(g.spawn, lo.spawn, hi.spawn) && within(g.sort, lo.sort, hi.sort) &&
+                      within(g.reduce, lo.reduce, hi.reduce) && within(g.merge, lo.merge, hi.merge) &&
+                      within(g.newdiag, lo.newdiag, hi.newdiag) && g.spawn_i == lo.spawn_i &&
+                      g.merge_i == lo.merge_i && g.sort_i == lo.sort_i;
+    if (keep) return;
+    c->w.sort_p = p;
+    c->plan = sized_grids(c, 2.0);
+    drop_graphs(c);
 }
 
 struct HostEntry {
@@ -606,6 +637,8 @@ fq_status upload_main(fq_ctx *c, const std::vector<HostEntry> &e)
     ctl.n_main_new = n;
     HIPCHK(c, h2d(c->stream, c->w.ctl, &ctl, sizeof(Ctl)));
     HIPCHK(c, hipStreamSynchronize(c->stream));
+    c->main_hint = n;
+    c->att_hint = ctl.n_att_new;
     c->spawn_hint = std::min<int64_t>(ctl.n_att_new / 4, c->spawn_cap);  // a fraction of the attempts spawns
     return FQ_OK;
 }
@@ -1264,7 +1297,7 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
                 c->graphs[b] = nullptr;
                 HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
                 for (int k = 0; k < nb; ++k) {
-                    hipError_t he = enqueue_iteration(c->w, c->lkind, c->grids, c->stream, nullptr);
+                    hipError_t he = enqueue_iteration(c->w, c->lkind, c->plan, c->stream, nullptr);
                     if (he != hipSuccess) {
                         hipGraph_t junk;
                         (void)hipStreamEndCapture(c->stream, &junk);
@@ -1285,7 +1318,7 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
             set_main_views(c);
         } else {
             for (int k = 0; k < nb; ++k) {
-                hipError_t he = enqueue_iteration(c->w, c->lkind, c->grids, c->stream, c->timing ? &evs[(size_t)k * NE] : nullptr);
+                hipError_t he = enqueue_iteration(c->w, c->lkind, c->plan, c->stream, c->timing ? &evs[(size_t)k * NE] : nullptr);
                 if (he != hipSuccess) return fail(c, FQ_EHIP, std::string("launch: ") + hipGetErrorString(he));
                 c->cur ^= 1;
                 set_main_views(c);
@@ -1368,6 +1401,8 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
             return fail(c, FQ_ECAPACITY, "main list capacity exceeded");
         }
         c->spawn_hint = (int64_t)ctl.n_spawn;
+        c->main_hint = ctl.n_main_new;
+        c->att_hint = ctl.n_att_new;
         fold_spawn_ratio(c, t0 + 1, stop);
         for (int64_t it = t0 + 1; it <= stop; ++it) {
             for (int r = 0; r < c->R; ++r) {

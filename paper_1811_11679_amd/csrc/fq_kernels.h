@@ -90,6 +90,9 @@ constexpr int SORT_TILE_MIN = 2048;
 // radix passes the plan may use
 constexpr int SORT_P_MAX = 4;
 
+// positions of the smallest merge tile
+constexpr int MERGE_TILE_MIN = 256;
+
 // spawn tiles: SP_T threads of SI attempts each (2, 4 or 8 for keys of up to
 // two words, chosen per context; 2 for longer keys, whose children take more
 // registers); the attempt partition is sized for the smallest tile
@@ -222,8 +225,9 @@ struct Grids {
     // depend on them): spawning attempts per thread (2, 4, 8; keys of up to two
     // words), merge positions per thread (1, 2, 4; keys of up to two words),
     // radix-sort keys per thread (8, 12, 16)
-    int spawn_i = 4, merge_i = 2, sort_i = 12;
+    int spawn_i = 4, merge_i = 4, sort_i = 12;
     int ccmc = 1024;  // blocks of the cluster-sampling kernel
+    int ss = 0;       // the deterministic space is active
 };
 
 // kernels of one iteration, in launch order (per-kernel timing slots; the

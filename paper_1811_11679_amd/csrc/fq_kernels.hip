@@ -13,51 +13,13 @@
 namespace fq {
 
 // ---------------------------------------------------------------------------
-// iteration prologue / epilogue
+// iteration epilogue of CCMC (its pair sum comes after the merge's last launch;
+// the other methods end there)
 // ---------------------------------------------------------------------------
-__global__ void k_begin(Work w)
+__global__ __launch_bounds__(END_T) void k_end(Work w, int nb_red, int nb_mrg)
 {
-    Ctl *c = w.ctl;
-    if (c->err) return;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        c->t += 1;
-        c->n_main = c->n_main_new;
-        c->n_spawn = 0;
-        c->n_att = c->n_att_new;
-        c->ccmc_n0 = 0;
-        c->ccmc_nex = 0;
-        c->n_single = 0;
-    }
-    for (int i = threadIdx.x; i < TK_COUNT; i += blockDim.x) c->tickets[i] = 0;
-    for (int i = threadIdx.x; i < 8 * 256; i += blockDim.x) (&c->hist[0][0])[i] = 0;
-    for (int i = threadIdx.x; i < w.R * (int)(sizeof(EstAcc) / 8); i += blockDim.x) ((long long *)w.acc)[i] = 0;
-}
-
-__global__ __launch_bounds__(1024) void k_end(Work w, int nb_red, int nb_mrg)
-{
-    // one block per replica, one wave per estimator field: fold the partials
-    // of the reduction and the merge into the accumulators, then record them
-    // in the history ring
-    const Ctl *c = w.ctl;
-    if (c->err) return;
-    const int r = blockIdx.x;
-    const int f = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (r < acc_rows(w.R) && f < EST_FIELDS) {
-        const long long *pr = w.part_red + (size_t)(r * EST_FIELDS + f) * PART_MAX_BLOCKS;
-        const long long *pm = w.part_mrg + (size_t)(r * EST_FIELDS + f) * PART_MAX_BLOCKS;
-        long long sum = 0;
-        for (int b = lane; b < nb_red; b += 64) sum += pr[b];
-        for (int b = lane; b < nb_mrg; b += 64) sum += pm[b];
-        sum = wave_sum<long long>(sum);
-        if (lane == 0) (&w.acc[r].nw)[f] += sum;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        EstAcc a = w.acc[r];
-        a.t = c->t;
-        w.hist[(size_t)(c->t % (uint32_t)w.hist_len) * w.R + r] = a;
-    }
+    if (w.ctl->err) return;
+    end_replica(w, blockIdx.x, nb_red, nb_mrg);
 }
 
 // ---------------------------------------------------------------------------
@@ -605,8 +567,7 @@ hipError_t enqueue_iteration(const Work &w, int kind, const Grids &g, hipStream_
     };
     hipError_t he;
     rec();
-    k_begin<<<1, 256, 0, s>>>(w);
-    rec();
+    rec();  // (the iteration begins in the attempt partition)
     if ((he = enqueue_spawn(0, kind, w, g, s)) != hipSuccess) return he;
     rec();
     if ((he = enqueue_spawn(1, kind, w, g, s)) != hipSuccess) return he;
@@ -634,22 +595,22 @@ hipError_t enqueue_iteration(const Work &w, int kind, const Grids &g, hipStream_
     rec();
     rec();
     rec();
-    k_det_gather<<<g.det, 256, 0, s>>>(w);
+    if (g.ss) k_det_gather<<<g.det, 256, 0, s>>>(w);
     rec();
-    if (w.ds.precision == 1)
+    if (g.ss && w.ds.precision == 1)
         k_det_project_split<<<g.det, 64 * DP_WAVES, 0, s>>>(w);
-    else
+    else if (g.ss)
         k_det_project_fp64<<<g.det, 256, 0, s>>>(w, 0);
     rec();
-    k_det_project_fp64<<<g.det, 256, 0, s>>>(w, 1);
+    if (g.ss && w.ds.precision == 1 && w.ds.check_period > 0) k_det_project_fp64<<<g.det, 256, 0, s>>>(w, 1);
     rec();
-    for (int part = 0; part < 3; ++part) {  // merge partition, merge, new-determinant diagonals
+    for (int part = 0; part < 3; ++part) {  // merge partition, merge, new-determinant diagonals (and the iteration's end)
         if ((he = enqueue_merge(part, kind, w, g, s)) != hipSuccess) return he;
         rec();
     }
     if (w.ccmc_trunc > 0) (void)enqueue_ccmc(1, kind, w, g, s);
     rec();
-    k_end<<<w.R, 1024, 0, s>>>(w, g.reduce, g.merge);
+    if (w.ccmc_trunc > 0) k_end<<<w.R, END_T, 0, s>>>(w, g.reduce, g.merge);
     rec();
     return hipGetLastError();
 }

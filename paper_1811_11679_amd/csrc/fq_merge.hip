@@ -15,57 +15,87 @@ namespace fq {
 // iteration epilogue folds the rows. The accumulators are a few addresses
 // that every block would otherwise hit with device-scope atomics.
 // ---------------------------------------------------------------------------
-struct LocalAcc {
-    long long v[EST_FIELDS];
+struct MergeAcc {
+    enum { NW, NOCC, FLIPS, DEATH, REJU, REJ, N };
+    long long v[N];
     int rep;
+    static __device__ __forceinline__ int field(int i)
+    {
+        return i == NW ? F_NW : i == NOCC ? F_NOCC : i == FLIPS ? F_FLIPS : i == DEATH ? F_DEATH : i == REJU ? F_REJU : F_REJ;
+    }
     __device__ void clear()
     {
 #pragma unroll
-        for (int i = 0; i < EST_FIELDS; ++i) v[i] = 0;
+        for (int i = 0; i < N; ++i) v[i] = 0;
+    }
+    // the thread's values to the block table, lane by lane
+    __device__ void spill(long long *tab, int rl, EstAcc *g)
+    {
+        if (rep < 0) return;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if (v[i]) acc_add(tab, rl, g, rep, field(i), v[i]);
+        clear();
+    }
+    __device__ __forceinline__ void use(int r, long long *tab, int rl, EstAcc *g)
+    {
+        if (r == rep) return;
+        spill(tab, rl, g);
+        rep = r;
+    }
+    // end of a kernel (all threads): reduced over the wave when its active
+    // lanes hold one replica
+    __device__ void finish(long long *tab, int rl, EstAcc *g)
+    {
+        const bool active = rep >= 0;
+        const uint64_t act = __ballot(active);
+        if (!act) return;
+        const int leader = __ffsll((unsigned long long)act) - 1;
+        const int rep0 = __shfl(rep, leader, 64);
+        if (__ballot(active && rep != rep0) == 0) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const long long sv = wave_sum<long long>(active ? v[i] : 0);
+                if (lane_id() == leader && sv != 0) acc_add(tab, rl, g, rep0, field(i), sv);
+            }
+        } else {
+            spill(tab, rl, g);
+        }
+        clear();
     }
 };
 
-// the thread's values to the block table, lane by lane
-__device__ __forceinline__ void acc_spill(LocalAcc &a, long long *tab, int rl, EstAcc *g)
+// Reference population (or trace) and exact terms of the projected energy of
+// one slot per lane, added at once: few entries have one, so they take no
+// registers between tiles. All lanes of the wave call it.
+__device__ void acc_terms(long long *tab, int rl, EstAcc *g, int rep, int32_t n0, bool term, double x)
 {
-    if (a.rep < 0) return;
-#pragma unroll
-    for (int f = 0; f < EST_FIELDS; ++f)
-        if (a.v[f]) acc_add(tab, rl, g, a.rep, f, a.v[f]);
-    a.clear();
-}
-
-__device__ __forceinline__ void acc_switch(LocalAcc &acc, int rep, long long *tab, int rl, EstAcc *g)
-{
-    if (rep == acc.rep) return;
-    acc_spill(acc, tab, rl, g);
-    acc.rep = rep;
-}
-
-// end of a kernel (all threads): reduce over the wave when its active lanes
-// hold one replica, then store the block's table as partial row blockIdx.x
-__device__ void acc_finish(LocalAcc &a, bool active, long long *tab, int rl, EstAcc *g, long long *part)
-{
-    const uint64_t act = __ballot(active);
-    if (act) {
-        const int leader = __ffsll((unsigned long long)act) - 1;
-        const int rep0 = __shfl(a.rep, leader, 64);
-        const bool uniform = __ballot(active && a.rep != rep0) == 0;
-        if (uniform) {
-#pragma unroll
-            for (int f = 0; f < EST_FIELDS; ++f) {
-                const long long sv = wave_sum<long long>(active ? a.v[f] : 0);
-                if (lane_id() == leader && sv != 0) acc_add(tab, rl, g, rep0, f, sv);
-            }
-        } else if (active) {
-            acc_spill(a, tab, rl, g);
+    long long l0 = 0, l1 = 0, l2 = 0, l3 = 0;
+    if (term) add_limbs4(l0, l1, l2, l3, x);
+    const uint64_t act = __ballot(n0 != 0 || term);
+    const int leader = __ffsll((unsigned long long)act) - 1;
+    const int rep0 = __shfl(rep, leader, 64);
+    const bool mine = n0 != 0 || term;
+    if (__popcll(act) > 4 && __ballot(mine && rep != rep0) == 0) {
+        l0 = wave_sum<long long>(l0);
+        l1 = wave_sum<long long>(l1);
+        l2 = wave_sum<long long>(l2);
+        l3 = wave_sum<long long>(l3);
+        const long long n = wave_sum<long long>((long long)n0);
+        if (lane_id() == leader) {
+            if (n) acc_add(tab, rl, g, rep0, F_N0, n);
+            if (l0) acc_add(tab, rl, g, rep0, F_L0, l0);
+            if (l1) acc_add(tab, rl, g, rep0, F_L1, l1);
+            if (l2) acc_add(tab, rl, g, rep0, F_L2, l2);
+            if (l3) acc_add(tab, rl, g, rep0, F_L3, l3);
         }
+    } else if (mine) {
+        if (n0) acc_add(tab, rl, g, rep, F_N0, n0);
+        if (l0) acc_add(tab, rl, g, rep, F_L0, l0);
+        if (l1) acc_add(tab, rl, g, rep, F_L1, l1);
+        if (l2) acc_add(tab, rl, g, rep, F_L2, l2);
+        if (l3) acc_add(tab, rl, g, rep, F_L3, l3);
     }
-    a.clear();
-    __syncthreads();
-    // partials are laid out [replica][field][block] so that the fold reads
-    // each (replica, field) as one contiguous run
-    for (int i = threadIdx.x; i < rl * EST_FIELDS; i += blockDim.x) part[(size_t)i * PART_MAX_BLOCKS + blockIdx.x] = tab[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -81,21 +111,16 @@ __device__ void acc_finish(LocalAcc &a, bool active, long long *tab, int rl, Est
 // merges its run of positions from LDS, writes each result into the source
 // slot, and the kept entries leave in merge order with coalesced stores.
 // ---------------------------------------------------------------------------
-// Keys of up to two words: 512 threads of two positions each, whose tile's
-// dependent phases (ticket, partition, staging, look-back) are shorter than
-// with 256 threads of four; two such blocks fit a compute unit's registers
-// and LDS. Longer keys: 256 threads of two positions (their LDS slice is
-// larger, and three such blocks per compute unit measured faster).
 // MI: merge positions per thread and tile, 1, 2 or 4 for keys of up to two
 // words (chosen per context), 2 for longer keys
 template <int W, int MI>
 struct MergeCfg {
-    static constexpr int T = W <= 2 ? 512 : 256;
-    static constexpr int I = MI;
-    static constexpr int TILE = T * I;
+    static constexpr int T = 256;
+    static constexpr int TILE = T * MI;
+    static constexpr int WPE = MI >= 4 || W > 2 ? 4 : (MI == 2 ? 5 : 6);  // waves per SIMD
 };
-static_assert(MergeCfg<1, 1>::TILE == 512 && MergeCfg<8, 2>::TILE == 512,
-              "the merge partition and status arrays are sized for 512-position tiles");
+static_assert(MergeCfg<1, 1>::TILE >= MERGE_TILE_MIN && MergeCfg<8, 2>::TILE >= MERGE_TILE_MIN,
+              "the merge partition and status arrays are sized for MERGE_TILE_MIN-position tiles");
 
 template <int W>
 __device__ __forceinline__ void load_key(const uint64_t *base, long long cap, long long i, uint64_t (&k)[W])
@@ -126,7 +151,7 @@ __device__ __forceinline__ bool le_ab(const Work &w, long long i, uint64_t si, l
 }
 
 template <int W, int MI>
-__global__ void k_merge_partition(Work w)
+__global__ __launch_bounds__(256) void k_merge_partition(Work w)
 {
     const Ctl *c = w.ctl;
     if (c->err) return;
@@ -147,11 +172,6 @@ __global__ void k_merge_partition(Work w)
 }
 
 
-__device__ __forceinline__ void add_limbs(long long (&v)[EST_FIELDS], double x)
-{
-    add_limbs4(v[F_L0], v[F_L1], v[F_L2], v[F_L3], x);
-}
-
 // spawning attempts of an entry holding p units: |p| for integer walkers,
 // ceil(|p| 2^-b) for fixed point, times mult (2 for DMQMC pairs: that many
 // at each end); 2^28 or more does not fit the counter's attempt field
@@ -164,44 +184,39 @@ __device__ __forceinline__ long long attempts_of(long long p, int bits, int mult
 }
 
 template <int KIND, int W, bool MULTI, int MI>
-__global__ __launch_bounds__((MergeCfg<W, MI>::T)) void k_merge(Work w)
+__global__ __launch_bounds__((MergeCfg<W, MI>::T), (MergeCfg<W, MI>::WPE)) void k_merge(Work w)
 {
     Ctl *c = w.ctl;
     if (c->err) return;
     constexpr int MG_T = MergeCfg<W, MI>::T, TILE = MergeCfg<W, MI>::TILE;
-    __shared__ uint64_t s_sk[TILE];
-    __shared__ uint64_t s_key[W][TILE];
-    __shared__ long long s_val[TILE];   // main: population, then the new one; spawned: sum
-    __shared__ double s_kd[TILE];       // K_ii - H_00
-    __shared__ int32_t s_meta[TILE];    // main: dslot; spawned: initiator flag, then dslot (-1)
-    __shared__ uint16_t s_src[TILE];    // merge position -> slot
-    __shared__ uint16_t s_dst[TILE];    // merge position -> rank among kept
-    __shared__ uint8_t s_keep[TILE];
+    __shared__ uint64_t s_sk[TILE];            // sort keys by slot
+    __shared__ uint32_t s_att[TILE];           // by merge position: kept << 31 | spawning attempts
+    __shared__ uint16_t s_rank[TILE];          // merge position -> rank among kept
     __shared__ uint64_t s_pa_sk, s_pa_key[W];  // main entry before the tile
     __shared__ uint64_t s_nb_sk, s_nb_key[W];  // spawned entry after the tile
     __shared__ long long s_nb_sum;
     __shared__ int s_pa_ok, s_nb_ok;
     __shared__ long long s_tile, s_base, s_abase;
-    __shared__ long long s_red[16];
+    __shared__ long long s_red[8];
     const long long na = c->n_main, nb = (long long)min(c->n_spawn, (unsigned long long)w.spawn_cap);
     const long long ntiles = (na + nb + TILE - 1) / TILE;
     const uint32_t t = c->t;
     const uint32_t epoch = epoch_of(t, 11), epoch_att = epoch_of(t, 13);
     const bool ss = c->ss_active != 0;
+    const int tid = threadIdx.x;
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     long long *tab = (long long *)dyn_lds;  // estimator table, acc_rows(R) rows
     const int rl = acc_rows(w.R);
     acc_table_clear(tab, rl);
-    LocalAcc acc;
+    MergeAcc acc;
     acc.clear();
     acc.rep = -1;
-    bool any = false;
     // time-step search: the largest K_ii of the entries this thread's death steps act on
     const bool ts = w.tau_search != 0;
     double kd_max = -INFINITY;
     int kd_rep = 0;
     for (;;) {
-        if (threadIdx.x == 0) s_tile = atomicAdd(&c->tickets[TK_MERGE], 1u);
+        if (tid == 0) s_tile = atomicAdd(&c->tickets[TK_MERGE], 1u);
         __syncthreads();
         const long long tile = s_tile;
         if (tile >= ntiles) break;
@@ -209,34 +224,42 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T)) void k_merge(Work w)
         const long long i0 = w.mpart[tile], i1 = w.mpart[tile + 1];
         const long long j0 = d0 - i0, j1 = d1 - i1;
         const int la = (int)(i1 - i0), lb = (int)(j1 - j0);
-        for (int q = threadIdx.x; q < la; q += MG_T) {
-            const long long g = i0 + q;
-            uint64_t k[W];
+        // slot it * MG_T + tid: main entries in [0, la), spawned ones in [la, la + lb)
+        uint64_t key[MI][W], sk[MI];
+        int32_t pop[MI], dsl[MI];  // main: population, slot in the deterministic space; spawned: -, flags
+        long long val[MI];         // main: the bits of K_ii - H_00; spawned: the sum
 #pragma unroll
-            for (int x = 0; x < W; ++x) {
-                k[x] = w.cur.key[(size_t)x * w.main_cap + g];
-                s_key[x][q] = k[x];
+        for (int it = 0; it < MI; ++it) {
+            const int q = it * MG_T + tid;
+            pop[it] = 0;
+            dsl[it] = -1;
+            if (q < la) {
+                const long long g = i0 + q;
+                load_key<W>(w.cur.key, w.main_cap, g, key[it]);
+                pop[it] = w.cur.pop[g];
+                val[it] = __double_as_longlong(w.cur.kdiag[g]);
+                if (ss) dsl[it] = w.cur.dslot[g];
+                sk[it] = stored_skey(MULTI, W) ? w.cur.skey[g] : hash64<W>(key[it]);
+                s_sk[q] = sk[it];
+            } else if (q < la + lb) {
+                const long long g = j0 + (q - la);
+                sk[it] = w.u.skey[g];
+                load_key<W>(w.u.key, w.spawn_cap, g, key[it]);
+                val[it] = w.u.sum[g];
+                dsl[it] = (int32_t)w.u.flag[g];
+                s_sk[q] = sk[it];
             }
-            s_sk[q] = stored_skey(MULTI, W) ? w.cur.skey[g] : hash64<W>(k);
-            s_val[q] = w.cur.pop[g];
-            s_kd[q] = w.cur.kdiag[g];
-            s_meta[q] = ss ? w.cur.dslot[g] : -1;
         }
-        for (int q = threadIdx.x; q < lb; q += MG_T) {
-            const long long g = j0 + q;
-            s_sk[la + q] = w.u.skey[g];
-#pragma unroll
-            for (int x = 0; x < W; ++x) s_key[x][la + q] = w.u.key[(size_t)x * w.spawn_cap + g];
-            s_val[la + q] = w.u.sum[g];
-            s_meta[la + q] = (int32_t)w.u.flag[g];
-        }
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             s_pa_ok = i0 > 0;
             if (i0 > 0) {
+                uint64_t k[W];
+                load_key<W>(w.cur.key, w.main_cap, i0 - 1, k);
 #pragma unroll
-                for (int x = 0; x < W; ++x) s_pa_key[x] = w.cur.key[(size_t)x * w.main_cap + i0 - 1];
-                s_pa_sk = stored_skey(MULTI, W) ? w.cur.skey[i0 - 1] : hash64<W>(s_pa_key);
+                for (int x = 0; x < W; ++x) s_pa_key[x] = k[x];
+                s_pa_sk = stored_skey(MULTI, W) ? w.cur.skey[i0 - 1] : hash64<W>(k);
             }
+        } else if (tid == 64) {
             s_nb_ok = j1 < nb;
             if (j1 < nb) {
                 s_nb_sk = w.u.skey[j1];
@@ -246,195 +269,186 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T)) void k_merge(Work w)
             }
         }
         __syncthreads();
-        auto le = [&](int a, int b) -> bool {  // A slot a <= B slot la + b
-            const uint64_t sa = s_sk[a], sb = s_sk[la + b];
-            if (sa != sb) return sa < sb;
-            int r = 0;
+        int mpos[MI];  // merge position of a kept slot, else -1
 #pragma unroll
-            for (int x = W - 1; x >= 0; --x)
-                if (r == 0) r = s_key[x][a] < s_key[x][la + b] ? -1 : (s_key[x][a] > s_key[x][la + b] ? 1 : 0);
-            return r <= 0;
-        };
-        auto eq_slots = [&](int p, int q) -> bool {
-            bool e = s_sk[p] == s_sk[q];
-#pragma unroll
-            for (int x = 0; x < W; ++x) e = e && s_key[x][p] == s_key[x][q];
-            return e;
-        };
-        const int dl = min((int)threadIdx.x * MI, la + lb);
-        int lo = max(0, dl - lb), hi = min(dl, la);
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (le(mid, dl - 1 - mid)) lo = mid + 1; else hi = mid;
-        }
-        int ia = lo, jb = dl - lo;
-        const int steps = min(MI, la + lb - dl);
-        for (int st = 0; st < steps; ++st) {
-            const int m = dl + st;
-            bool takeA;
-            if (ia >= la) takeA = false;
-            else if (jb >= lb) takeA = true;
-            else takeA = le(ia, jb);
-            if (takeA) {
-                const int a = ia++;
-                const uint64_t sk = s_sk[a];
-                const int32_t n0 = (int32_t)s_val[a];
-                const int32_t dsl = s_meta[a];
-                const int rep = MULTI ? (int)skey_rep(sk, w.rb) : 0;
-                acc_switch(acc, rep, tab, rl, w.acc);
-                any = true;
-                // matching spawned determinant: the next unconsumed one
+        for (int it = 0; it < MI; ++it) {
+            const int q = it * MG_T + tid;
+            mpos[it] = -1;
+            if (q < la) {
+                const uint64_t x = sk[it];
+                const int rep = MULTI ? (int)skey_rep(x, w.rb) : 0;
+                const RepParams &rp = w.rep[rep];
+                acc.use(rep, tab, rl, w.acc);
+                // spawned entries before it, and the one on the same determinant
+                int j = 0, hi = lb;
+                while (j < hi) {
+                    const int mid = (j + hi) >> 1;
+                    if (s_sk[la + mid] < x) j = mid + 1; else hi = mid;
+                }
                 long long add = 0;
-                if (jb < lb) {
-                    if (eq_slots(a, la + jb)) add = s_val[la + jb];
-                } else if (s_nb_ok && s_nb_sk == sk) {
+                while (j < lb && s_sk[la + j] == x) {
+                    uint64_t kb[W];
+                    load_key<W>(w.u.key, w.spawn_cap, j0 + j, kb);
+                    const int r = key_cmp<W>(kb, key[it]);
+                    if (r == 0) add = w.u.sum[j0 + j];
+                    if (r >= 0) break;
+                    ++j;
+                }
+                if (j == lb && s_nb_ok && s_nb_sk == x) {
                     bool e = true;
 #pragma unroll
-                    for (int x = 0; x < W; ++x) e = e && s_nb_key[x] == s_key[x][a];
+                    for (int y = 0; y < W; ++y) e = e && s_nb_key[y] == key[it][y];
                     if (e) add = s_nb_sum;
                 }
+                const int32_t n0 = pop[it];
                 long long v;
-                if (ss && dsl >= 0) {
-                    v = (long long)n0 + w.ds.delta[(size_t)rep * w.ds.n + dsl];
+                if (ss && dsl[it] >= 0) {
+                    v = (long long)n0 + w.ds.delta[(size_t)rep * w.ds.n + dsl[it]];
                 } else if (n0 != 0) {
-                    const RepParams &rp = w.rep[rep];
+                    const double kd = __longlong_as_double(val[it]);
                     if (ts) {
                         if (MULTI && rep != kd_rep) {
                             if (kd_max > -INFINITY) ts_put<true>(w, kd_rep, kd_max);
                             kd_max = -INFINITY;
                             kd_rep = rep;
                         }
-                        kd_max = fmax(kd_max, s_kd[a]);
+                        kd_max = fmax(kd_max, kd);
                     }
                     const double an = (double)(n0 < 0 ? -(long long)n0 : (long long)n0);
-                    const double mm = (rp.tau * (s_kd[a] - w.shift[rep])) * an;
-                    uint64_t h = sk;
-                    if constexpr (MULTI) {
-                        uint64_t key[W];
-#pragma unroll
-                        for (int x = 0; x < W; ++x) key[x] = s_key[x][a];
-                        h = hash64<W>(key);
-                    }
+                    const double mm = (rp.tau * (kd - w.shift[rep])) * an;
+                    const uint64_t h = MULTI ? hash64<W>(key[it]) : x;
                     const U4 r = draw(TAG_DEATH, 0, t, h, rp.k0, rp.k1);
                     const double u = u53(r.x, r.y);
                     if (!(fabs(mm) < 0x1p40)) atomicOr(&c->err, ERR_OVERFLOW);
                     const long long k = mm >= 0.0 ? sround(mm, u) : -sround(-mm, u);
                     const long long sg = n0 > 0 ? 1 : -1;
                     v = (long long)n0 - sg * k;
-                    if ((v > 0 && n0 < 0) || (v < 0 && n0 > 0)) acc.v[F_FLIPS] += 1;
+                    if ((v > 0 && n0 < 0) || (v < 0 && n0 > 0)) acc.v[MergeAcc::FLIPS] += 1;
                 } else {
                     v = 0;
                 }
-                acc.v[F_DEATH] += v;
+                acc.v[MergeAcc::DEATH] += v;
                 v += add;
                 if (v > 2147483647ll || v < -2147483647ll) atomicOr(&c->err, ERR_OVERFLOW);
-                s_val[a] = v;
-                s_src[m] = (uint16_t)a;
-                s_keep[m] = (v != 0 || dsl >= 0) ? 1 : 0;
-            } else {
-                const int b = jb++;
-                const int slot = la + b;
-                // matched with the preceding main entry: that entry's thread added it
-                bool matched;
-                if (ia > 0) {
-                    matched = eq_slots(ia - 1, slot);
-                } else {
-                    matched = s_pa_ok && s_pa_sk == s_sk[slot];
-#pragma unroll
-                    for (int x = 0; x < W; ++x) matched = matched && s_pa_key[x] == s_key[x][slot];
+                pop[it] = (int32_t)v;
+                uint32_t a = 0;
+                if (v != 0 || dsl[it] >= 0) {
+                    mpos[it] = q + j;
+                    a = 0x80000000u | (uint32_t)attempts_of(v, rp.bits, w.dm == 1 ? 2 : 1, c);
                 }
-                s_src[m] = (uint16_t)slot;
-                s_keep[m] = 0;
-                if (!matched && !(s_meta[slot] & (int32_t)UNIQ_FILLER)) {
-                    const long long sum = s_val[slot];
-                    const int32_t fl = s_meta[slot];
-                    const int rep = MULTI ? (int)skey_rep(s_sk[slot], w.rb) : 0;
+                s_att[q + j] = a;
+            } else if (q < la + lb) {
+                const uint64_t x = sk[it];
+                // main entries up to it; is the last of them the same determinant
+                int i = 0, hi = la;
+                while (i < hi) {
+                    const int mid = (i + hi) >> 1;
+                    if (s_sk[mid] <= x) i = mid + 1; else hi = mid;
+                }
+                bool matched = false;
+                while (i > 0 && s_sk[i - 1] == x) {
+                    uint64_t ka[W];
+                    load_key<W>(w.cur.key, w.main_cap, i0 + i - 1, ka);
+                    const int r = key_cmp<W>(ka, key[it]);
+                    matched = r == 0;  // that entry's thread added the sum
+                    if (r <= 0) break;
+                    --i;
+                }
+                if (i == 0 && s_pa_ok && s_pa_sk == x) {
+                    matched = true;
+#pragma unroll
+                    for (int y = 0; y < W; ++y) matched = matched && s_pa_key[y] == key[it][y];
+                }
+                const int m = q - la + i;
+                uint32_t a = 0;
+                const uint32_t fl = (uint32_t)dsl[it];
+                dsl[it] = -1;
+                if (!matched && !(fl & UNIQ_FILLER)) {
+                    const long long sum = val[it];
+                    const int rep = MULTI ? (int)skey_rep(x, w.rb) : 0;
                     const RepParams &rp = w.rep[rep];
-                    acc_switch(acc, rep, tab, rl, w.acc);
-                    any = true;
-                    const bool accept = (!rp.initiator || fl) && sum != 0;
-                    if (accept) {
+                    acc.use(rep, tab, rl, w.acc);
+                    if ((!rp.initiator || fl) && sum != 0) {
                         if (sum > 2147483647ll || sum < -2147483647ll) atomicOr(&c->err, ERR_OVERFLOW);
+                        mpos[it] = m;
+                        pop[it] = (int32_t)sum;
                         // K_jj - H_00 is filled in by k_new_diag (off the merge's critical path)
-                        s_kd[slot] = __longlong_as_double(0x7FF8000000000000ll);
-                        s_meta[slot] = -1;
-                        s_keep[m] = 1;
+                        val[it] = 0x7FF8000000000000ll;
+                        a = 0x80000000u | (uint32_t)attempts_of(sum, rp.bits, w.dm == 1 ? 2 : 1, c);
                     } else {
-                        acc.v[F_REJU] += sum < 0 ? -sum : sum;
-                        acc.v[F_REJ] += sum;
+                        acc.v[MergeAcc::REJU] += sum < 0 ? -sum : sum;
+                        acc.v[MergeAcc::REJ] += sum;
                     }
                 }
+                s_att[m] = a;
             }
-        }
-        // ranks of the kept entries in merge order, and their spawning attempts
-        // for the next iteration (the attempt prefix replaces a separate scan)
-        int cnt = 0;
-        long long asum = 0;
-        for (int st = 0; st < steps; ++st) {
-            const int m = dl + st;
-            if (!s_keep[m]) continue;
-            ++cnt;
-            const int slot = s_src[m];
-            const int rep = MULTI ? (int)skey_rep(s_sk[slot], w.rb) : 0;
-            asum += attempts_of(s_val[slot], w.rep[rep].bits, w.dm == 1 ? 2 : 1, c);
-        }
-        long long tot, atot, ex, aex;
-        block_excl_scan2((long long)cnt, asum, ex, aex, tot, atot, s_red);
-        if (threadIdx.x < 64) {
-            const long long lb_ = lookback(w.st_merge, tile, epoch, tot);
-            if (threadIdx.x == 0) s_base = lb_;
-        } else if (threadIdx.x < 128) {
-            const long long lb_ = lookback(w.st_att, tile, epoch_att, atot);
-            if (threadIdx.x == 64) s_abase = lb_;
-        }
-        {
-            int r = (int)ex;
-            for (int st = 0; st < steps; ++st)
-                if (s_keep[dl + st]) s_dst[dl + st] = (uint16_t)r++;
         }
         __syncthreads();
-        if (s_base + tot <= w.main_cap) {
-            long long ar = s_abase + aex;
-            for (int st = 0; st < steps; ++st) {
-                const int m = dl + st;
-                if (!s_keep[m]) continue;
-                const int slot = s_src[m];
-                const int rep = MULTI ? (int)skey_rep(s_sk[slot], w.rb) : 0;
-                w.att_off[s_base + s_dst[m]] = ar;
-                ar += attempts_of(s_val[slot], w.rep[rep].bits, w.dm == 1 ? 2 : 1, c);
-            }
-        }
-        const long long obase = s_base;
-        if (obase + tot > w.main_cap) {
-            if (threadIdx.x == 0) atomicOr(&c->err, ERR_MAIN_CAP);
-        } else {
-            for (int m = threadIdx.x; m < la + lb; m += MG_T) {
-                if (!s_keep[m]) continue;
-                const long long o = obase + s_dst[m];
-                const int slot = s_src[m];
-                const uint64_t sk = s_sk[slot];
-                const int rep = MULTI ? (int)skey_rep(sk, w.rb) : 0;
-                const RepParams &rp = w.rep[rep];
-                const DevSys &sy = w.sys[rp.sys];
-                const int32_t p = (int32_t)s_val[slot];
-                const int32_t ds = s_meta[slot];
-                if (stored_skey(MULTI, W)) w.nxt.skey[o] = sk;
-                uint64_t key[W];
+        // ranks of the kept entries in merge order, and their spawning attempts
+        // for the next iteration (the attempt prefix replaces a separate scan);
+        // one word carries both: kept entries above bit 44, attempts below
+        // (fewer than 2^28 each)
+        const int p0 = tid * MI;
+        uint32_t at[MI];
+        long long loc = 0;
 #pragma unroll
-                for (int x = 0; x < W; ++x) {
-                    key[x] = s_key[x][slot];
-                    w.nxt.key[(size_t)x * w.main_cap + o] = key[x];
+        for (int st = 0; st < MI; ++st) {
+            at[st] = p0 + st < la + lb ? s_att[p0 + st] : 0u;
+            loc += ((long long)(at[st] >> 31) << 44) + (long long)(at[st] & 0x7FFFFFFFu);
+        }
+        long long total;
+        const long long excl = block_excl_scan<long long>(loc, total, s_red);
+        const long long tot = total >> 44, atot = total & ((1ll << 44) - 1);
+        if (tid < 64) {
+            const long long lb_ = lookback(w.st_merge, tile, epoch, tot);
+            if (tid == 0) s_base = lb_;
+        } else if (tid < 128) {
+            const long long lb_ = lookback(w.st_att, tile, epoch_att, atot);
+            if (tid == 64) s_abase = lb_;
+        }
+        const int r0 = (int)(excl >> 44);
+        {
+            int r = r0;
+#pragma unroll
+            for (int st = 0; st < MI; ++st)
+                if (at[st] >> 31) s_rank[p0 + st] = (uint16_t)r++;
+        }
+        __syncthreads();
+        const long long obase = s_base;
+        const bool fits = obase + tot <= w.main_cap;
+        if (!fits) {
+            if (tid == 0) atomicOr(&c->err, ERR_MAIN_CAP);
+        } else {
+            long long ar = s_abase + (excl & ((1ll << 44) - 1));
+            long long o = obase + r0;
+#pragma unroll
+            for (int st = 0; st < MI; ++st)
+                if (at[st] >> 31) {
+                    w.att_off[o++] = ar;
+                    ar += (long long)(at[st] & 0x7FFFFFFFu);
                 }
+        }
+#pragma unroll
+        for (int it = 0; it < MI; ++it) {
+            const bool put = fits && mpos[it] >= 0;
+            bool n0_term = false, term = false;
+            double x = 0.0;
+            const int rep = MULTI && put ? (int)skey_rep(sk[it], w.rb) : 0;
+            const int32_t p = pop[it];
+            if (put) {
+                const long long o = obase + s_rank[mpos[it]];
+                const DevSys &sy = w.sys[w.rep[rep].sys];
+                if (stored_skey(MULTI, W)) w.nxt.skey[o] = sk[it];
+#pragma unroll
+                for (int y = 0; y < W; ++y) w.nxt.key[(size_t)y * w.main_cap + o] = key[it][y];
                 w.nxt.pop[o] = p;
-                w.nxt.kdiag[o] = s_kd[slot];
-                w.newdet[o] = slot >= la ? 1 : 0;
-                if (ss) w.nxt.dslot[o] = ds;
-                if (ds >= 0) w.ds.pos[(size_t)rep * w.ds.n + ds] = (int32_t)o;
-                const long long ap = p < 0 ? -(long long)p : (long long)p;
-                acc_switch(acc, rep, tab, rl, w.acc);
-                any = true;
-                acc.v[F_NW] += ap;
-                acc.v[F_NOCC] += 1;
+                w.nxt.kdiag[o] = __longlong_as_double(val[it]);
+                w.newdet[o] = it * MG_T + tid >= la ? 1 : 0;
+                if (ss) w.nxt.dslot[o] = dsl[it];
+                if (dsl[it] >= 0) w.ds.pos[(size_t)rep * w.ds.n + dsl[it]] = (int32_t)o;
+                acc.use(rep, tab, rl, w.acc);
+                acc.v[MergeAcc::NW] += p < 0 ? -(long long)p : (long long)p;
+                acc.v[MergeAcc::NOCC] += 1;
                 if constexpr (is_pair(KIND)) {
                     // density matrix (Sec. 2.3): the trace sum_i rho_ii and
                     // Tr(rho H) = sum rho_ij H_ji over pairs at most doubly excited
@@ -442,41 +456,41 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T)) void k_merge(Work w)
                     uint64_t a[WH], b[WH];
                     int nd = 0;
 #pragma unroll
-                    for (int x = 0; x < WH; ++x) {
-                        a[x] = key[x];
-                        b[x] = key[WH + x];
-                        nd += __popcll(a[x] ^ b[x]);
+                    for (int y = 0; y < WH; ++y) {
+                        a[y] = key[it][y];
+                        b[y] = key[it][WH + y];
+                        nd += __popcll(a[y] ^ b[y]);
                     }
-                    if (nd == 0) {
-                        acc.v[F_N0] += p;
-                        add_limbs(acc.v, diag_element<BK, WH>(sy, a) * (double)p);
-                    } else if (nd == 2 || nd == 4) {
-                        add_limbs(acc.v, hij<BK, WH>(sy, b, a) * (double)p);
-                    }
+                    n0_term = nd == 0;
+                    term = nd == 0 || nd == 2 || nd == 4;
+                    if (nd == 0)
+                        x = diag_element<BK, WH>(sy, a) * (double)p;
+                    else if (term)
+                        x = hij<BK, WH>(sy, b, a) * (double)p;
                 } else {
                     const uint64_t(&ref)[W] = *(const uint64_t(*)[W])sy.ref;
                     int nd = 0;
 #pragma unroll
-                    for (int x = 0; x < W; ++x) nd += __popcll(key[x] ^ ref[x]);
-                    if (nd == 0) {
-                        acc.v[F_N0] += p;
-                    } else if (nd == 2 || nd == 4) {
-                        const double hv = hij<KIND, W>(sy, ref, key);
-                        add_limbs(acc.v, hv * (double)p);
-                    }
+                    for (int y = 0; y < W; ++y) nd += __popcll(key[it][y] ^ ref[y]);
+                    n0_term = nd == 0;
+                    term = nd == 2 || nd == 4;
+                    if (term) x = hij<KIND, W>(sy, ref, key[it]) * (double)p;
                 }
             }
+            if (__any(n0_term || term)) acc_terms(tab, rl, w.acc, rep, n0_term ? p : 0, term, x);
         }
-        if (tile == ntiles - 1 && threadIdx.x == 0) {
+        if (tile == ntiles - 1 && tid == 0) {
             c->n_main_new = obase + tot;
-            if (obase + tot <= w.main_cap) w.att_off[obase + tot] = s_abase + atot;
+            if (fits) w.att_off[obase + tot] = s_abase + atot;
             c->n_att_new = s_abase + atot;
         }
         __syncthreads();
     }
-    acc_finish(acc, any && acc.rep >= 0, tab, rl, w.acc, w.part_mrg);
+    acc.finish(tab, rl, w.acc);
+    __syncthreads();
+    for (int i = tid; i < rl * EST_FIELDS; i += MG_T) w.part_mrg[(size_t)i * PART_MAX_BLOCKS + blockIdx.x] = tab[i];
     if (ts) ts_finish<true>(w, kd_max, kd_rep, kd_max > -INFINITY);
-    if (blockIdx.x == 0 && threadIdx.x == 0 && ntiles == 0) {
+    if (blockIdx.x == 0 && tid == 0 && ntiles == 0) {
         c->n_main_new = 0;
         w.att_off[0] = 0;
         c->n_att_new = 0;
@@ -493,11 +507,18 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T)) void k_merge(Work w)
 constexpr int ND_T = 512, ND_CHUNK = 16384;
 static_assert(ND_CHUNK == ND_T * 32, "each thread scans 32 new-determinant flags");
 
+// The blocks beyond nd_blocks end the iteration, one replica each: the merge is
+// the last kernel that adds to the accumulators.
 template <int KIND, int W>
-__global__ __launch_bounds__(ND_T) void k_new_diag(Work w)
+__global__ __launch_bounds__(ND_T) void k_new_diag(Work w, int nd_blocks, int nb_red, int nb_mrg)
 {
     const Ctl *c = w.ctl;
     if (c->err) return;
+    static_assert(ND_T == END_T, "the blocks that end the iteration have the size of the others");
+    if ((int)blockIdx.x >= nd_blocks) {
+        end_replica(w, (int)blockIdx.x - nd_blocks, nb_red, nb_mrg);
+        return;
+    }
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     __shared__ uint16_t s_q[ND_CHUNK];  // offsets of the chunk's new determinants
     __shared__ int s_n;
@@ -543,7 +564,7 @@ __global__ __launch_bounds__(ND_T) void k_new_diag(Work w)
             lK = t2;
         }
     }
-    for (long long base = (long long)blockIdx.x * ND_CHUNK; base < n; base += (long long)gridDim.x * ND_CHUNK) {
+    for (long long base = (long long)blockIdx.x * ND_CHUNK; base < n; base += (long long)nd_blocks * ND_CHUNK) {
         if (threadIdx.x == 0) s_n = 0;
         __syncthreads();
         // the merge's new-determinant flags, 32 per thread in two 16-byte loads
@@ -613,7 +634,8 @@ template <int KIND, int W>
 static void launch_merge_kind(int part, const Work &w, const Grids &g, hipStream_t s)
 {
     if (part == 2) {
-        k_new_diag<KIND, W><<<g.newdiag, ND_T, w.lds_diag, s>>>(w);
+        const int ends = w.ccmc_trunc > 0 ? 0 : w.R;  // CCMC ends after its pair sum
+        k_new_diag<KIND, W><<<g.newdiag + ends, ND_T, w.lds_diag, s>>>(w, g.newdiag, g.reduce, g.merge);
         return;
     }
     const int mi = W <= 2 ? g.merge_i : 2;
@@ -636,7 +658,7 @@ int merge_occupancy(bool wide)
     int nb = 1;
     const hipError_t e =
         wide ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_merge<K_UEG, 8, false, 2>, MergeCfg<8, 2>::T, 0)
-             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_merge<K_UEG, 2, false, 2>, MergeCfg<2, 2>::T, 0);
+             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_merge<K_UEG, 2, false, 4>, MergeCfg<2, 4>::T, 0);
     if (e != hipSuccess) nb = 1;
     return nb < 1 ? 1 : nb;
 }

@@ -262,6 +262,33 @@ __device__ double entry_kdiag(const Work &w, const DevSys &sy, const uint64_t (&
     }
 }
 
+// End of an iteration, by one block of END_T threads per replica: folds the
+// partials of the reduction and the merge into the accumulators, one wave per
+// field, then records them in the history ring.
+constexpr int END_T = 512;
+static __device__ void end_replica(const Work &w, int r, int nb_red, int nb_mrg)
+{
+    const int lane = threadIdx.x & 63;
+    if (r < acc_rows(w.R)) {
+        for (int f = threadIdx.x >> 6; f < EST_FIELDS; f += END_T / 64) {
+            const long long *pr = w.part_red + (size_t)(r * EST_FIELDS + f) * PART_MAX_BLOCKS;
+            const long long *pm = w.part_mrg + (size_t)(r * EST_FIELDS + f) * PART_MAX_BLOCKS;
+            long long sum = 0;
+            for (int b = lane; b < nb_red; b += 64) sum += pr[b];
+            for (int b = lane; b < nb_mrg; b += 64) sum += pm[b];
+            sum = wave_sum<long long>(sum);
+            if (lane == 0) (&w.acc[r].nw)[f] += sum;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t t = w.ctl->t;
+        EstAcc a = w.acc[r];
+        a.t = t;
+        w.hist[(size_t)(t % (uint32_t)w.hist_len) * w.R + r] = a;
+    }
+}
+
 // calls fn<KIND, W> for the kernel kind and key width of a context
 #define FQ_DISPATCH(fn, ...)                                                                  \
     switch (kind * 16 + w.W) {                                                               \

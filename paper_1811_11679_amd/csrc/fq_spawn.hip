@@ -26,14 +26,31 @@ __device__ __forceinline__ long long upper_bound_ll(const long long *a, long lon
     return lo;
 }
 
-__global__ void k_spawn_partition(Work w, int span_len)
+// Also the iteration's beginning: block 0 advances the counters and clears
+// what the iteration accumulates. The other blocks read only the counts of the
+// list the last iteration wrote, which it leaves alone.
+__global__ __launch_bounds__(256) void k_spawn_partition(Work w, int span_len)
 {
-    const Ctl *c = w.ctl;
+    Ctl *c = w.ctl;
     if (c->err) return;
-    const long long total = c->n_att, n = c->n_main;
+    const long long total = c->n_att_new, n = c->n_main_new;
     const long long nspans = (total + span_len - 1) / span_len;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) {
+            c->t += 1;
+            c->n_main = n;
+            c->n_spawn = 0;
+            c->n_att = total;
+            c->ccmc_n0 = 0;
+            c->ccmc_nex = 0;
+            c->n_single = 0;
+        }
+        for (int i = threadIdx.x; i < TK_COUNT; i += blockDim.x) c->tickets[i] = 0;
+        for (int i = threadIdx.x; i < w.sort_p * 256; i += blockDim.x) c->hist[7 - (i >> 8)][i & 255] = 0;
+        for (int i = threadIdx.x; i < w.R * (int)(sizeof(EstAcc) / 8); i += blockDim.x) ((long long *)w.acc)[i] = 0;
+    }
     if (nspans + 1 > w.span_cap) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&((Ctl *)c)->err, ERR_SPAWN_CAP);
+        if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&c->err, ERR_SPAWN_CAP);
         return;
     }
     for (long long s = (long long)blockIdx.x * blockDim.x + threadIdx.x; s <= nspans;

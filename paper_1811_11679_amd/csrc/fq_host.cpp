@@ -228,7 +228,7 @@ size_t table_bytes(const HostSys &s)
 
 struct Layout {
     size_t total = 0;
-    size_t ctl, acc, hist, shift, rep, sys, tables, att, span, mpart, st_scan, st_sort, st_merge, st_att;
+    size_t ctl, acc, hist, shift, rep, sys, tables, att, span, mpart, mtile, mrun, mpop, msrc, st_scan, st_sort;
     size_t part_red, part_mrg, newdet;
     size_t main[2][6];
     size_t sp[7];
@@ -289,11 +289,13 @@ Layout make_layout(int R, int W, int64_t mcap, int64_t scap, int64_t tables, int
     L.att = take(8 * (size_t)(mcap + 1));
     L.span = take(8 * (size_t)(span_capacity(mcap, scap, W) + 2));
     L.mpart = take(8 * (size_t)(tiles_of(mcap + scap, MERGE_TILE_MIN) + 2));
+    L.mtile = take(8 * (size_t)tiles_of(mcap + scap, MERGE_TILE_MIN));
+    L.mrun = take(16 * (size_t)PART_MAX_BLOCKS);
+    L.mpop = take(4 * (size_t)(mcap + scap));
+    L.msrc = take(2 * (size_t)(mcap + scap));
     L.newdet = take((size_t)mcap + 16);
     L.st_scan = take(8 * (size_t)tiles_of(mcap, 2048));
     L.st_sort = take(8 * 256 * (size_t)tiles_of(scap, SORT_TILE_MIN));
-    L.st_merge = take(8 * (size_t)tiles_of(mcap + scap, MERGE_TILE_MIN));
-    L.st_att = take(8 * (size_t)tiles_of(mcap + scap, MERGE_TILE_MIN));
     L.part_red = take(8 * (size_t)PART_MAX_BLOCKS * acc_rows(R) * EST_FIELDS);
     L.part_mrg = take(8 * (size_t)PART_MAX_BLOCKS * acc_rows(R) * EST_FIELDS);
     for (int b = 0; b < 2; ++b) {
@@ -528,11 +530,12 @@ Grids sized_grids(const fq_ctx *c, double room)
         return (int)std::max<int64_t>(1, std::min<int64_t>(cap, n));
     };
     const int64_t ns = c->spawn_hint, nm = c->main_hint + c->spawn_hint;
-    g.part = fit(c->grids.part, std::max(c->att_hint / SPAN_MIN, nm / MERGE_TILE_MIN), 256);
+    g.part = fit(c->grids.part, c->att_hint / SPAN_MIN, 256);
     g.spawn = fit(c->grids.spawn, c->att_hint, SP_T * (c->W <= 2 ? c->grids.spawn_i : 2));
     g.sort = fit(c->grids.sort, ns, 256 * c->grids.sort_i);
     g.reduce = fit(c->grids.reduce, ns, 768);
     g.merge = fit(c->grids.merge, nm, MERGE_TILE_MIN * (c->W <= 2 ? c->grids.merge_i : 2));
+    g.move = fit(c->grids.move, nm, MERGE_TILE_MIN * (c->W <= 2 ? c->grids.merge_i : 2));
     g.newdiag = fit(c->grids.newdiag, nm, 16384);
     g.ss = c->ss_active ? 1 : 0;
     return g;
@@ -945,11 +948,13 @@ fq_status init_system(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc, con
     w.att_off = (long long *)(c->ws + c->L.att);
     w.span_lo = (long long *)(c->ws + c->L.span);
     w.mpart = (long long *)(c->ws + c->L.mpart);
+    w.mtile = (long long *)(c->ws + c->L.mtile);
+    w.mrun = (long long *)(c->ws + c->L.mrun);
+    w.mpop = (int32_t *)(c->ws + c->L.mpop);
+    w.msrc = (uint16_t *)(c->ws + c->L.msrc);
     w.newdet = (uint8_t *)(c->ws + c->L.newdet);
     w.st_scan = (unsigned long long *)(c->ws + c->L.st_scan);
     w.st_sort = (unsigned long long *)(c->ws + c->L.st_sort);
-    w.st_merge = (unsigned long long *)(c->ws + c->L.st_merge);
-    w.st_att = (unsigned long long *)(c->ws + c->L.st_att);
     w.part_red = (long long *)(c->ws + c->L.part_red);
     w.part_mrg = (long long *)(c->ws + c->L.part_mrg);
     w.sp.skey = (uint64_t *)(c->ws + c->L.sp[0]);
@@ -1102,6 +1107,7 @@ fq_status init_system(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc, con
     c->grids.sort = ncu * occupancy_blocks(0);
     c->grids.merge = std::min(ncu * occupancy_blocks(c->W <= 2 ? 1 : 5), PART_MAX_BLOCKS);
     c->grids.reduce = std::min(ncu * occupancy_blocks(2), PART_MAX_BLOCKS);
+    c->grids.move = ncu * 8;
     c->grids.part = ncu * 4;
     c->grids.spawn = ncu * occupancy_blocks(4);
     // diagonal tables staged in LDS by the single-replica new-determinant kernel

@@ -34,7 +34,6 @@ enum : uint32_t {
 enum : int {
     TK_SCAN = 0,
     TK_SORT = 1,   // 8 passes: 1..8
-    TK_MERGE = 11,
     TK_SPAWN = 12,
     TK_CCMC = 13,
     TK_COUNT = 16,
@@ -184,9 +183,14 @@ struct Work {
     const DevSys *sys;     // [n_sys]
     long long *att_off;    // [main_cap + 1]
     long long *span_lo;    // [spans + 1]
-    long long *mpart;      // merge partition [tiles + 1]
+    // merge: split of each tile [tiles + 1], its kept entries and attempts
+    // [tiles], the same summed over each block's run [2 blocks], and by merge
+    // position the new population and the slot of its tile it comes from
+    long long *mpart, *mtile, *mrun;
+    int32_t *mpop;
+    uint16_t *msrc;
     uint8_t *newdet;       // [main_cap]: 1 where the merge wrote a new determinant (K_jj still to compute)
-    unsigned long long *st_scan, *st_sort, *st_merge, *st_att;  // look-back status
+    unsigned long long *st_scan, *st_sort;  // look-back status
     // per-block estimator partials of the reduction and the merge:
     // [block][acc_rows(R)][EST_FIELDS], folded into acc by the epilogue
     long long *part_red, *part_mrg;
@@ -218,7 +222,7 @@ struct Work {
 
 // launch geometry of the persistent kernels
 struct Grids {
-    int scan, part, spawn, sort, reduce, merge, det;
+    int scan, part, spawn, sort, reduce, merge, move, det;
     int spawn_lds;  // dynamic LDS bytes of the spawn kernel
     int newdiag;    // blocks of the new-determinant diagonal kernel
     // tile shapes (compile-time variants chosen at run time; results do not
@@ -242,7 +246,7 @@ hipError_t enqueue_ccmc(int stage, int kind, const Work &w, const Grids &g, hipS
 // spawning: part 0 the attempt partition, 1 the spawn
 hipError_t enqueue_spawn(int part, int kind, const Work &w, const Grids &g, hipStream_t s);
 int spawn_occupancy();
-// merge: part 0 the merge partition, 1 the merge, 2 the diagonal elements of the new determinants
+// merge: part 0 the decisions, 1 the move, 2 the diagonal elements of the new determinants (and the iteration's end)
 hipError_t enqueue_merge(int part, int kind, const Work &w, const Grids &g, hipStream_t s);
 int merge_occupancy(bool wide);
 // segmented reduction of the spawned list after `passes` radix passes

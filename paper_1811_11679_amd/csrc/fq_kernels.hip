@@ -604,10 +604,12 @@ hipError_t enqueue_iteration(const Work &w, int kind, const Grids &g, hipStream_
     rec();
     if (g.ss && w.ds.precision == 1 && w.ds.check_period > 0) k_det_project_fp64<<<g.det, 256, 0, s>>>(w, 1);
     rec();
-    for (int part = 0; part < 3; ++part) {  // merge partition, merge, new-determinant diagonals (and the iteration's end)
-        if ((he = enqueue_merge(part, kind, w, g, s)) != hipSuccess) return he;
-        rec();
-    }
+    rec();  // (a merge block finds its own splits)
+    if ((he = enqueue_merge(0, kind, w, g, s)) != hipSuccess) return he;
+    if ((he = enqueue_merge(1, kind, w, g, s)) != hipSuccess) return he;
+    rec();
+    if ((he = enqueue_merge(2, kind, w, g, s)) != hipSuccess) return he;
+    rec();
     if (w.ccmc_trunc > 0) (void)enqueue_ccmc(1, kind, w, g, s);
     rec();
     if (w.ccmc_trunc > 0) k_end<<<w.R, END_T, 0, s>>>(w, g.reduce, g.merge);

@@ -106,10 +106,15 @@ __device__ void acc_terms(long long *tab, int rl, EstAcc *g, int rep, int32_t n0
 // the estimators of the new list (tutorial appendix) and the attempt counts of
 // the next iteration. Ties in the merge order put the main entry first.
 //
-// A tile's slices of both lists are staged in LDS with coalesced loads (main
-// entries in slots [0, la), spawned ones in [la, la + lb)); every thread
-// merges its run of positions from LDS, writes each result into the source
-// slot, and the kept entries leave in merge order with coalesced stores.
+// Two kernels. k_merge decides: for each merge position the new population
+// and the slot it comes from, and how many entries each tile keeps. k_move
+// writes the kept entries at their places. A block takes a run of neighbouring
+// tiles, so a block's place in the output is a sum over the runs before it,
+// read when k_move starts; no tile waits for another. (One kernel with a
+// decoupled look-back moved 65 bytes per entry instead of 101 but took 2890 us
+// for 6e7 entries: its time fitted 8.6 ns per tile + 2310 us, a tile being held
+// up by every tile in flight before it, and wider look-back reads made it
+// slower, 3650 us.)
 // ---------------------------------------------------------------------------
 // MI: merge positions per thread and tile, 1, 2 or 4 for keys of up to two
 // words (chosen per context), 2 for longer keys
@@ -150,38 +155,95 @@ __device__ __forceinline__ bool le_ab(const Work &w, long long i, uint64_t si, l
     return key_cmp<W>(a, b) <= 0;
 }
 
-template <int W, int MI>
-__global__ __launch_bounds__(256) void k_merge_partition(Work w)
-{
-    const Ctl *c = w.ctl;
-    if (c->err) return;
-    constexpr int TILE = MergeCfg<W, MI>::TILE;
-    const long long na = c->n_main, nb = (long long)min(c->n_spawn, (unsigned long long)w.spawn_cap);
-    const long long ntiles = (na + nb + TILE - 1) / TILE;
-    for (long long tile = (long long)blockIdx.x * blockDim.x + threadIdx.x; tile <= ntiles;
-         tile += (long long)gridDim.x * blockDim.x) {
-        const long long d = min(tile * TILE, na + nb);
-        long long lo = max(0ll, d - nb), hi = min(d, na);
-        while (lo < hi) {
-            const long long mid = (lo + hi) >> 1;
-            const long long j = d - 1 - mid;
-            if (le_ab<W>(w, mid, main_skey<W>(w, mid), j, w.u.skey[j])) lo = mid + 1; else hi = mid;
+// Split of merge diagonal d: how many main entries come before it. Without a
+// replica field the sort keys are hashes, spread evenly, so the split is looked
+// for within a few standard deviations of its expected place first.
+struct SplitRange {
+    long long lo, hi, a, b;
+    __device__ SplitRange(const Work &w, long long d, long long na, long long nb)
+    {
+        lo = max(0ll, d - nb);
+        hi = min(d, na);
+        a = lo;
+        b = hi;
+        if (w.rb == 0 && hi - lo > 4096) {
+            const double g = (double)d * ((double)na / (double)(na + nb)), s = 4.0 * sqrt((double)hi);
+            a = min(max(lo, (long long)(g - s)), hi);
+            b = max(min(hi, (long long)(g + s)), lo);
         }
-        w.mpart[tile] = lo;
     }
+};
+
+template <int W>
+__device__ __forceinline__ bool split_after(const Work &w, long long d, long long i)
+{
+    const long long j = d - 1 - i;
+    return le_ab<W>(w, i, main_skey<W>(w, i), j, w.u.skey[j]);
 }
 
+// by one thread
+template <int W>
+__device__ long long split_thread(const Work &w, long long d, long long na, long long nb)
+{
+    SplitRange r(w, d, na, nb);
+    long long lo = r.lo, hi = r.hi;
+    if (r.a > lo) {
+        if (split_after<W>(w, d, r.a - 1)) lo = r.a; else hi = r.a - 1;
+    }
+    if (r.b < hi && r.b >= lo) {
+        if (split_after<W>(w, d, r.b)) lo = r.b + 1; else hi = r.b;
+    }
+    while (lo < hi) {
+        const long long mid = (lo + hi) >> 1;
+        if (split_after<W>(w, d, mid)) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+// by a wavefront, 64 places at once
+template <int W>
+__device__ long long split_wave(const Work &w, long long d, long long na, long long nb)
+{
+    SplitRange r(w, d, na, nb);
+    const int lane = lane_id();
+    long long lo = r.lo, hi = r.hi;
+    if (r.a > lo || r.b < hi) {
+        const bool in = lane == 0 ? r.a > lo : lane == 1 && r.b < hi;
+        const uint64_t yes = __ballot(in && split_after<W>(w, d, lane == 0 ? r.a - 1 : r.b));
+        if (r.a > lo) {
+            if (yes & 1) lo = r.a; else hi = r.a - 1;
+        }
+        if (r.b < hi && r.b >= lo) {
+            if (yes & 2) lo = r.b + 1; else hi = r.b;
+        }
+    }
+    while (lo < hi) {
+        const long long step = (hi - lo + 63) >> 6;
+        const long long p = lo + lane * step;
+        const int cnt = __popcll(__ballot(p < hi && split_after<W>(w, d, p)));  // they come first
+        if (cnt == 0) return lo;
+        hi = min(hi, lo + cnt * step);
+        lo += (cnt - 1) * step + 1;
+    }
+    return lo;
+}
 
 // spawning attempts of an entry holding p units: |p| for integer walkers,
 // ceil(|p| 2^-b) for fixed point, times mult (2 for DMQMC pairs: that many
 // at each end); 2^28 or more does not fit the counter's attempt field
-__device__ __forceinline__ long long attempts_of(long long p, int bits, int mult, Ctl *c)
+constexpr long long MAX_ATTEMPTS = 1ll << 28;
+__device__ __forceinline__ long long attempts_of(long long p, int bits, int mult)
 {
     const long long ap = p < 0 ? -p : p;
-    const long long n = mult * (bits == 0 ? ap : (ap + (1ll << bits) - 1) >> bits);
-    if (n >= (1ll << 28)) atomicOr(&c->err, ERR_ATTEMPTS);
-    return n;
+    return mult * (bits == 0 ? ap : (ap + (1ll << bits) - 1) >> bits);
 }
+
+// a tile's totals in one word: kept entries above MT_SHIFT, attempts below
+// (fewer than 2^28 each for at most 1024 entries)
+constexpr int MT_SHIFT = 44;
+constexpr long long MT_MASK = (1ll << MT_SHIFT) - 1;
+// place of a merge position's entry: slot of its tile, and whether it is kept
+constexpr uint32_t MS_KEEP = 0x8000u;
 
 template <int KIND, int W, bool MULTI, int MI>
 __global__ __launch_bounds__((MergeCfg<W, MI>::T), (MergeCfg<W, MI>::WPE)) void k_merge(Work w)
@@ -190,18 +252,18 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T), (MergeCfg<W, MI>::WPE)) void 
     if (c->err) return;
     constexpr int MG_T = MergeCfg<W, MI>::T, TILE = MergeCfg<W, MI>::TILE;
     __shared__ uint64_t s_sk[TILE];            // sort keys by slot
-    __shared__ uint32_t s_att[TILE];           // by merge position: kept << 31 | spawning attempts
-    __shared__ uint16_t s_rank[TILE];          // merge position -> rank among kept
+    constexpr int CHUNK = 64;                  // tiles whose splits are found at once
+    __shared__ long long s_split[CHUNK + 1];
     __shared__ uint64_t s_pa_sk, s_pa_key[W];  // main entry before the tile
     __shared__ uint64_t s_nb_sk, s_nb_key[W];  // spawned entry after the tile
     __shared__ long long s_nb_sum;
     __shared__ int s_pa_ok, s_nb_ok;
-    __shared__ long long s_tile, s_base, s_abase;
-    __shared__ long long s_red[8];
+    __shared__ long long s_red[MG_T / 64];
     const long long na = c->n_main, nb = (long long)min(c->n_spawn, (unsigned long long)w.spawn_cap);
     const long long ntiles = (na + nb + TILE - 1) / TILE;
+    const long long run = (ntiles + gridDim.x - 1) / gridDim.x;  // tiles of a block
+    const long long t0 = min((long long)blockIdx.x * run, ntiles), t1 = min(t0 + run, ntiles);
     const uint32_t t = c->t;
-    const uint32_t epoch = epoch_of(t, 11), epoch_att = epoch_of(t, 13);
     const bool ss = c->ss_active != 0;
     const int tid = threadIdx.x;
     extern __shared__ __align__(16) unsigned char dyn_lds[];
@@ -215,13 +277,26 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T), (MergeCfg<W, MI>::WPE)) void 
     const bool ts = w.tau_search != 0;
     double kd_max = -INFINITY;
     int kd_rep = 0;
-    for (;;) {
-        if (tid == 0) s_tile = atomicAdd(&c->tickets[TK_MERGE], 1u);
-        __syncthreads();
-        const long long tile = s_tile;
-        if (tile >= ntiles) break;
+    long long run_cnt = 0, run_att = 0;  // thread 0: of the block's tiles
+    for (long long tile = t0; tile < t1; ++tile) {
+        const int at = (int)((tile - t0) % CHUNK);
+        if (at == 0) {
+            // the splits of the next tiles: a wavefront each while they are few
+            const int n = (int)min((long long)CHUNK, t1 - tile) + 1;
+            __syncthreads();
+            if (n <= 8) {
+                for (int q = tid >> 6; q < n; q += MG_T / 64) {
+                    const long long i = split_wave<W>(w, min((tile + q) * TILE, na + nb), na, nb);
+                    if (lane_id() == 0) s_split[q] = i;
+                }
+            } else if (tid < n) {
+                s_split[tid] = split_thread<W>(w, min((tile + tid) * TILE, na + nb), na, nb);
+            }
+            __syncthreads();
+            for (int q = tid; q < n; q += MG_T) w.mpart[tile + q] = s_split[q];
+        }
         const long long d0 = tile * TILE, d1 = min(d0 + TILE, na + nb);
-        const long long i0 = w.mpart[tile], i1 = w.mpart[tile + 1];
+        const long long i0 = s_split[at], i1 = s_split[at + 1];
         const long long j0 = d0 - i0, j1 = d1 - i1;
         const int la = (int)(i1 - i0), lb = (int)(j1 - j0);
         // slot it * MG_T + tid: main entries in [0, la), spawned ones in [la, la + lb)
@@ -269,14 +344,15 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T), (MergeCfg<W, MI>::WPE)) void 
             }
         }
         __syncthreads();
-        int mpos[MI];  // merge position of a kept slot, else -1
+        long long loc = 0;
 #pragma unroll
         for (int it = 0; it < MI; ++it) {
             const int q = it * MG_T + tid;
-            mpos[it] = -1;
+            bool kept = false;
+            int rep = 0;
             if (q < la) {
                 const uint64_t x = sk[it];
-                const int rep = MULTI ? (int)skey_rep(x, w.rb) : 0;
+                rep = MULTI ? (int)skey_rep(x, w.rb) : 0;
                 const RepParams &rp = w.rep[rep];
                 acc.use(rep, tab, rl, w.acc);
                 // spawned entries before it, and the one on the same determinant
@@ -331,12 +407,9 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T), (MergeCfg<W, MI>::WPE)) void 
                 v += add;
                 if (v > 2147483647ll || v < -2147483647ll) atomicOr(&c->err, ERR_OVERFLOW);
                 pop[it] = (int32_t)v;
-                uint32_t a = 0;
-                if (v != 0 || dsl[it] >= 0) {
-                    mpos[it] = q + j;
-                    a = 0x80000000u | (uint32_t)attempts_of(v, rp.bits, w.dm == 1 ? 2 : 1, c);
-                }
-                s_att[q + j] = a;
+                kept = v != 0 || dsl[it] >= 0;
+                w.mpop[d0 + q + j] = (int32_t)v;
+                w.msrc[d0 + q + j] = (uint16_t)((uint32_t)q | (kept ? MS_KEEP : 0u));
             } else if (q < la + lb) {
                 const uint64_t x = sk[it];
                 // main entries up to it; is the last of them the same determinant
@@ -359,94 +432,33 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T), (MergeCfg<W, MI>::WPE)) void 
 #pragma unroll
                     for (int y = 0; y < W; ++y) matched = matched && s_pa_key[y] == key[it][y];
                 }
-                const int m = q - la + i;
-                uint32_t a = 0;
                 const uint32_t fl = (uint32_t)dsl[it];
-                dsl[it] = -1;
                 if (!matched && !(fl & UNIQ_FILLER)) {
                     const long long sum = val[it];
-                    const int rep = MULTI ? (int)skey_rep(x, w.rb) : 0;
+                    rep = MULTI ? (int)skey_rep(x, w.rb) : 0;
                     const RepParams &rp = w.rep[rep];
                     acc.use(rep, tab, rl, w.acc);
                     if ((!rp.initiator || fl) && sum != 0) {
                         if (sum > 2147483647ll || sum < -2147483647ll) atomicOr(&c->err, ERR_OVERFLOW);
-                        mpos[it] = m;
+                        kept = true;
                         pop[it] = (int32_t)sum;
-                        // K_jj - H_00 is filled in by k_new_diag (off the merge's critical path)
-                        val[it] = 0x7FF8000000000000ll;
-                        a = 0x80000000u | (uint32_t)attempts_of(sum, rp.bits, w.dm == 1 ? 2 : 1, c);
                     } else {
                         acc.v[MergeAcc::REJU] += sum < 0 ? -sum : sum;
                         acc.v[MergeAcc::REJ] += sum;
                     }
                 }
-                s_att[m] = a;
+                w.mpop[d0 + (q - la + i)] = pop[it];
+                w.msrc[d0 + (q - la + i)] = (uint16_t)((uint32_t)q | (kept ? MS_KEEP : 0u));
             }
-        }
-        __syncthreads();
-        // ranks of the kept entries in merge order, and their spawning attempts
-        // for the next iteration (the attempt prefix replaces a separate scan);
-        // one word carries both: kept entries above bit 44, attempts below
-        // (fewer than 2^28 each)
-        const int p0 = tid * MI;
-        uint32_t at[MI];
-        long long loc = 0;
-#pragma unroll
-        for (int st = 0; st < MI; ++st) {
-            at[st] = p0 + st < la + lb ? s_att[p0 + st] : 0u;
-            loc += ((long long)(at[st] >> 31) << 44) + (long long)(at[st] & 0x7FFFFFFFu);
-        }
-        long long total;
-        const long long excl = block_excl_scan<long long>(loc, total, s_red);
-        const long long tot = total >> 44, atot = total & ((1ll << 44) - 1);
-        if (tid < 64) {
-            const long long lb_ = lookback(w.st_merge, tile, epoch, tot);
-            if (tid == 0) s_base = lb_;
-        } else if (tid < 128) {
-            const long long lb_ = lookback(w.st_att, tile, epoch_att, atot);
-            if (tid == 64) s_abase = lb_;
-        }
-        const int r0 = (int)(excl >> 44);
-        {
-            int r = r0;
-#pragma unroll
-            for (int st = 0; st < MI; ++st)
-                if (at[st] >> 31) s_rank[p0 + st] = (uint16_t)r++;
-        }
-        __syncthreads();
-        const long long obase = s_base;
-        const bool fits = obase + tot <= w.main_cap;
-        if (!fits) {
-            if (tid == 0) atomicOr(&c->err, ERR_MAIN_CAP);
-        } else {
-            long long ar = s_abase + (excl & ((1ll << 44) - 1));
-            long long o = obase + r0;
-#pragma unroll
-            for (int st = 0; st < MI; ++st)
-                if (at[st] >> 31) {
-                    w.att_off[o++] = ar;
-                    ar += (long long)(at[st] & 0x7FFFFFFFu);
-                }
-        }
-#pragma unroll
-        for (int it = 0; it < MI; ++it) {
-            const bool put = fits && mpos[it] >= 0;
+            // estimators and next iteration's attempts of a kept entry
             bool n0_term = false, term = false;
-            double x = 0.0;
-            const int rep = MULTI && put ? (int)skey_rep(sk[it], w.rb) : 0;
+            double e = 0.0;
             const int32_t p = pop[it];
-            if (put) {
-                const long long o = obase + s_rank[mpos[it]];
+            if (kept) {
                 const DevSys &sy = w.sys[w.rep[rep].sys];
-                if (stored_skey(MULTI, W)) w.nxt.skey[o] = sk[it];
-#pragma unroll
-                for (int y = 0; y < W; ++y) w.nxt.key[(size_t)y * w.main_cap + o] = key[it][y];
-                w.nxt.pop[o] = p;
-                w.nxt.kdiag[o] = __longlong_as_double(val[it]);
-                w.newdet[o] = it * MG_T + tid >= la ? 1 : 0;
-                if (ss) w.nxt.dslot[o] = dsl[it];
-                if (dsl[it] >= 0) w.ds.pos[(size_t)rep * w.ds.n + dsl[it]] = (int32_t)o;
-                acc.use(rep, tab, rl, w.acc);
+                const long long natt = attempts_of(p, w.rep[rep].bits, w.dm == 1 ? 2 : 1);
+                if (natt >= MAX_ATTEMPTS) atomicOr(&c->err, ERR_ATTEMPTS);
+                loc += (1ll << MT_SHIFT) + natt;
                 acc.v[MergeAcc::NW] += p < 0 ? -(long long)p : (long long)p;
                 acc.v[MergeAcc::NOCC] += 1;
                 if constexpr (is_pair(KIND)) {
@@ -464,9 +476,9 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T), (MergeCfg<W, MI>::WPE)) void 
                     n0_term = nd == 0;
                     term = nd == 0 || nd == 2 || nd == 4;
                     if (nd == 0)
-                        x = diag_element<BK, WH>(sy, a) * (double)p;
+                        e = diag_element<BK, WH>(sy, a) * (double)p;
                     else if (term)
-                        x = hij<BK, WH>(sy, b, a) * (double)p;
+                        e = hij<BK, WH>(sy, b, a) * (double)p;
                 } else {
                     const uint64_t(&ref)[W] = *(const uint64_t(*)[W])sy.ref;
                     int nd = 0;
@@ -474,26 +486,162 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T), (MergeCfg<W, MI>::WPE)) void 
                     for (int y = 0; y < W; ++y) nd += __popcll(key[it][y] ^ ref[y]);
                     n0_term = nd == 0;
                     term = nd == 2 || nd == 4;
-                    if (term) x = hij<KIND, W>(sy, ref, key[it]) * (double)p;
+                    if (term) e = hij<KIND, W>(sy, ref, key[it]) * (double)p;
                 }
             }
-            if (__any(n0_term || term)) acc_terms(tab, rl, w.acc, rep, n0_term ? p : 0, term, x);
+            if (__any(n0_term || term)) acc_terms(tab, rl, w.acc, rep, n0_term ? p : 0, term, e);
         }
-        if (tile == ntiles - 1 && tid == 0) {
-            c->n_main_new = obase + tot;
-            if (fits) w.att_off[obase + tot] = s_abase + atot;
-            c->n_att_new = s_abase + atot;
+        loc = wave_sum<long long>(loc);
+        if (lane_id() == 0) s_red[tid >> 6] = loc;
+        __syncthreads();  // (also: the tile's sort keys have been read)
+        if (tid == 0) {
+            long long tot = 0;
+#pragma unroll
+            for (int q = 0; q < MG_T / 64; ++q) tot += s_red[q];
+            w.mtile[tile] = tot;
+            run_cnt += tot >> MT_SHIFT;
+            run_att += tot & MT_MASK;
         }
-        __syncthreads();
+    }
+    if (tid == 0) {
+        w.mrun[2 * blockIdx.x] = run_cnt;
+        w.mrun[2 * blockIdx.x + 1] = run_att;
     }
     acc.finish(tab, rl, w.acc);
     __syncthreads();
     for (int i = tid; i < rl * EST_FIELDS; i += MG_T) w.part_mrg[(size_t)i * PART_MAX_BLOCKS + blockIdx.x] = tab[i];
     if (ts) ts_finish<true>(w, kd_max, kd_rep, kd_max > -INFINITY);
-    if (blockIdx.x == 0 && tid == 0 && ntiles == 0) {
+}
+
+// Writes the entries k_merge has kept: merge position by merge position, each
+// from its slot of the old list or of the spawned one. runs: blocks k_merge
+// had. Bound: HBM; 6 bytes per position and 8W + 12 per entry read, 8W + 21
+// written (one instance, no deterministic space).
+constexpr int MV_T = 256;
+template <int W, bool MULTI, int MI>
+__global__ __launch_bounds__(MV_T) void k_move(Work w, int runs)
+{
+    Ctl *c = w.ctl;
+    if (c->err) return;
+    constexpr int TILE = MergeCfg<W, MI>::TILE, WAVES = MV_T / 64;
+    static_assert(TILE == MV_T * MI, "a thread takes MI positions");
+    __shared__ long long s_w[WAVES];
+    __shared__ long long s_red[16];
+    const int tid = threadIdx.x, lane = lane_id(), wid = tid >> 6;
+    const bool ss = c->ss_active != 0;
+    const long long na = c->n_main, nb = (long long)min(c->n_spawn, (unsigned long long)w.spawn_cap);
+    const long long ntiles = (na + nb + TILE - 1) / TILE;
+    const long long run = (ntiles + runs - 1) / runs, per = (ntiles + gridDim.x - 1) / gridDim.x;
+    const long long t0 = min((long long)blockIdx.x * per, ntiles), t1 = min(t0 + per, ntiles);
+    if (ntiles == 0 && blockIdx.x == 0 && tid == 0) {
         c->n_main_new = 0;
         w.att_off[0] = 0;
         c->n_att_new = 0;
+    }
+    if (t0 >= t1) return;
+    // entries kept and attempts before this block's first tile
+    long long base, abase;
+    {
+        long long n = 0, a = 0, xn, xa;
+        const long long r0 = t0 / run;
+        for (long long q = tid; q < r0; q += MV_T) {
+            n += w.mrun[2 * q];
+            a += w.mrun[2 * q + 1];
+        }
+        for (long long q = r0 * run + tid; q < t0; q += MV_T) {
+            n += w.mtile[q] >> MT_SHIFT;
+            a += w.mtile[q] & MT_MASK;
+        }
+        block_excl_scan2(n, a, xn, xa, base, abase, s_red);
+    }
+    for (long long tile = t0; tile < t1; ++tile) {
+        const long long d0 = tile * TILE, d1 = min(d0 + TILE, na + nb);
+        const long long i0 = w.mpart[tile], i1 = w.mpart[tile + 1];
+        const long long j0 = d0 - i0;
+        const int la = (int)(i1 - i0);
+        // position wid * 64 MI + it * 64 + lane of the tile
+        uint32_t src[MI];
+        int32_t p[MI];
+        long long x[MI];  // kept and attempts of the wave's positions up to this one
+        long long sum = 0;
+#pragma unroll
+        for (int it = 0; it < MI; ++it) {
+            const long long d = d0 + wid * 64 * MI + it * 64 + lane;
+            src[it] = d < d1 ? w.msrc[d] : 0u;
+            p[it] = d < d1 ? w.mpop[d] : 0;
+        }
+        uint64_t sk[MI];
+#pragma unroll
+        for (int it = 0; it < MI; ++it) {
+            long long v = 0;
+            sk[it] = 0;
+            if (src[it] & MS_KEEP) {
+                const int q = (int)(src[it] & (MS_KEEP - 1));
+                if constexpr (stored_skey(MULTI, W)) sk[it] = q < la ? w.cur.skey[i0 + q] : w.u.skey[j0 + q - la];
+                const int rep = MULTI ? (int)skey_rep(sk[it], w.rb) : 0;
+                v = (1ll << MT_SHIFT) + attempts_of(p[it], w.rep[rep].bits, w.dm == 1 ? 2 : 1);
+            }
+            x[it] = v;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const long long y = __shfl_up(x[it], o, 64);
+                if (lane >= o) x[it] += y;
+            }
+            const long long tot = __shfl(x[it], 63, 64);
+            x[it] += sum - v;
+            sum += tot;
+        }
+        __syncthreads();
+        if (lane == 0) s_w[wid] = sum;
+        __syncthreads();
+        long long before = 0, total = 0;
+#pragma unroll
+        for (int q = 0; q < WAVES; ++q) {
+            if (q < wid) before += s_w[q];
+            total += s_w[q];
+        }
+        const long long tot = total >> MT_SHIFT, atot = total & MT_MASK;
+        const bool fits = base + tot <= w.main_cap;
+        if (!fits) {
+            if (tid == 0) atomicOr(&c->err, ERR_MAIN_CAP);
+        } else {
+#pragma unroll
+            for (int it = 0; it < MI; ++it) {
+                if (!(src[it] & MS_KEEP)) continue;
+                const int q = (int)(src[it] & (MS_KEEP - 1));
+                const bool old = q < la;
+                const long long g = old ? i0 + q : j0 + (q - la);
+                const long long e = before + x[it];
+                const long long o = base + (e >> MT_SHIFT);
+                uint64_t key[W];
+                if (old)
+                    load_key<W>(w.cur.key, w.main_cap, g, key);
+                else
+                    load_key<W>(w.u.key, w.spawn_cap, g, key);
+                // K_jj - H_00 of a new determinant is filled in by k_new_diag
+                const double kd = old ? w.cur.kdiag[g] : __longlong_as_double(0x7FF8000000000000ll);
+                if constexpr (stored_skey(MULTI, W)) w.nxt.skey[o] = sk[it];
+#pragma unroll
+                for (int y = 0; y < W; ++y) w.nxt.key[(size_t)y * w.main_cap + o] = key[y];
+                w.nxt.pop[o] = p[it];
+                w.nxt.kdiag[o] = kd;
+                w.newdet[o] = old ? 0 : 1;
+                w.att_off[o] = abase + (e & MT_MASK);
+                if (ss) {
+                    const int rep = MULTI ? (int)skey_rep(sk[it], w.rb) : 0;
+                    const int32_t ds = old ? w.cur.dslot[g] : -1;
+                    w.nxt.dslot[o] = ds;
+                    if (ds >= 0) w.ds.pos[(size_t)rep * w.ds.n + ds] = (int32_t)o;
+                }
+            }
+        }
+        base += tot;
+        abase += atot;
+        if (tile == ntiles - 1 && tid == 0) {
+            c->n_main_new = base;
+            if (fits) w.att_off[base] = abase;
+            c->n_att_new = abase;
+        }
     }
 }
 
@@ -622,12 +770,14 @@ template <int KIND, int W, int MI>
 static void launch_merge(int part, const Work &w, const Grids &g, hipStream_t s)
 {
     const int accb = acc_rows(w.R) * EST_FIELDS * 8;
-    if (part == 0)
-        k_merge_partition<W, MI><<<g.part, 256, 0, s>>>(w);
-    else if (w.R > 1)
+    if (part == 0 && w.R > 1)
         k_merge<KIND, W, true, MI><<<g.merge, MergeCfg<W, MI>::T, accb, s>>>(w);
-    else
+    else if (part == 0)
         k_merge<KIND, W, false, MI><<<g.merge, MergeCfg<W, MI>::T, accb, s>>>(w);
+    else if (w.R > 1)
+        k_move<W, true, MI><<<g.move, MV_T, 0, s>>>(w, g.merge);
+    else
+        k_move<W, false, MI><<<g.move, MV_T, 0, s>>>(w, g.merge);
 }
 
 template <int KIND, int W>

@@ -515,11 +515,11 @@ __device__ bool gen_hubbard(const DevSys &s, const uint64_t (&D)[W], uint32_t w0
     return true;
 }
 
-// UEG: uniform pair of occupied spin-orbitals, uniform A (same spin as the
-// pair, or any spin for an opposite-spin pair), B fixed by momentum.
+// UEG: the pair of occupied spin-orbitals P < Q the first word draws, the i-th
+// and the j-th of the determinant
 template <int W>
-__device__ bool gen_ueg(const UegTables &s, const uint64_t (&D)[W], uint32_t w0, uint32_t w1,
-                        uint64_t (&child)[W], double &pgen, double &h)
+__device__ __forceinline__ void ueg_pair(const UegTables &s, const uint64_t (&D)[W], uint32_t w0, int &i, int &j, int &P,
+                                         int &Q)
 {
     const int N = s.nel;
     const uint32_t npairs = (uint32_t)(N * (N - 1) / 2);
@@ -527,12 +527,23 @@ __device__ bool gen_ueg(const UegTables &s, const uint64_t (&D)[W], uint32_t w0,
     // lexicographic unranking: i is the largest with i (2N - i - 1) / 2 <= k
     // (square-root estimate, then an exact integer correction)
     const float bb = (float)(2 * N - 1);
-    int i = (int)((bb - sqrtf(bb * bb - 8.0f * (float)k)) * 0.5f);
+    i = (int)((bb - sqrtf(bb * bb - 8.0f * (float)k)) * 0.5f);
     i = i < 0 ? 0 : (i > N - 2 ? N - 2 : i);
     while (i > 0 && i * (2 * N - i - 1) / 2 > k) --i;
     while (i < N - 2 && (i + 1) * (2 * N - i - 2) / 2 <= k) ++i;
-    const int j = i + 1 + (k - i * (2 * N - i - 1) / 2);
-    const int P = select_bit<W>(D, i), Q = select_bit<W>(D, j);
+    j = i + 1 + (k - i * (2 * N - i - 1) / 2);
+    P = select_bit<W>(D, i);
+    Q = select_bit<W>(D, j);
+}
+
+// UEG: uniform pair of occupied spin-orbitals, uniform A (same spin as the
+// pair, or any spin for an opposite-spin pair), B fixed by momentum.
+template <int W>
+__device__ bool gen_ueg(const UegTables &s, const uint64_t (&D)[W], uint32_t w0, uint32_t w1,
+                        uint64_t (&child)[W], double &pgen, double &h)
+{
+    int i, j, P, Q;
+    ueg_pair<W>(s, D, w0, i, j, P, Q);
     const int sP = P & 1, sQ = Q & 1, M = s.M;
     int A;
     if (sP == sQ)

@@ -537,6 +537,8 @@ Grids sized_grids(const fq_ctx *c, double room)
     g.merge = fit(c->grids.merge, nm, MERGE_TILE_MIN * (c->W <= 2 ? c->grids.merge_i : 2));
     g.move = fit(c->grids.move, nm, MERGE_TILE_MIN * (c->W <= 2 ? c->grids.merge_i : 2));
     g.newdiag = fit(c->grids.newdiag, nm, 16384);
+    // (about as many cluster selections as attempts; a block stages the prefix for a few passes)
+    g.ccmc = fit(c->grids.ccmc, c->att_hint, 4 * 256);
     g.ss = c->ss_active ? 1 : 0;
     return g;
 }
@@ -552,7 +554,7 @@ void choose_plan(fq_ctx *c)
     const bool keep = p == c->w.sort_p && g.ss == lo.ss && within(g.part, lo.part, hi.part) &&
                       within(g.spawn, lo.spawn, hi.spawn) && within(g.sort, lo.sort, hi.sort) &&
                       within(g.reduce, lo.reduce, hi.reduce) && within(g.merge, lo.merge, hi.merge) &&
-                      within(g.newdiag, lo.newdiag, hi.newdiag) && g.spawn_i == lo.spawn_i &&
+                      within(g.newdiag, lo.newdiag, hi.newdiag) && within(g.ccmc, lo.ccmc, hi.ccmc) && g.spawn_i == lo.spawn_i &&
                       g.merge_i == lo.merge_i && g.sort_i == lo.sort_i;
     if (keep) return;
     c->w.sort_p = p;

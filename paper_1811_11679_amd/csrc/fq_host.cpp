@@ -1128,7 +1128,7 @@ fq_status init_system(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc, con
     // heat-bath pair weights (upper triangle) staged in LDS by the single-replica spawn kernel
     if (one_system && c->kind == FQ_MOLECULAR) {
         const size_t nso = (size_t)c->sys[0].n_so;
-        const size_t bytes = 8 * (nso * (nso - 1) / 2);
+        const size_t bytes = 8 * (nso * (nso - 1) / 2 + 1);
         if (bytes <= 32768) {
             c->grids.spawn_lds = (int)bytes;
             w.lds_tables = (int32_t)bytes;

@@ -115,6 +115,7 @@ __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
             }
             tt[x] = sy0.hb_S[P * nso + P + 1 + rem];
         }
+        if (threadIdx.x == 0) tt[ntri] = 0.0;  // the weight of no pair
         hb_tri = tt;
     }
     if constexpr (LT && KIND == K_UEG) {
@@ -229,7 +230,8 @@ __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
                 }
                 rep[it] = MULTI ? skey_rep(psk, w.rb) : 0u;
                 const RepParams &rp = w.rep[MULTI ? rep[it] : 0u];
-                const DevSys &sy = w.sys[rp.sys];
+                // tables are staged only when all replicas share one system
+                const DevSys &sy = w.sys[LT ? w.rep[0].sys : rp.sys];
                 const uint64_t h = (!MULTI && W > 2) ? psk : hash64<W>(key);
                 const long long an = n0 < 0 ? -(long long)n0 : (long long)n0;
                 const bool pin_d = ss && dsl >= 0;

@@ -366,7 +366,8 @@ fq_status fq_get_launch(const fq_ctx *ctx, int32_t *blocks, int32_t n);
  * [1] merge positions per thread (1, 2 or 4; tiles of 256 threads), [2]
  * radix-sort keys per thread (8, 12 or 16; tiles of 256 threads). [0] and [1]
  * apply to determinant keys of one or two words (longer keys and pair keys
- * use 2 and 2, resp. 4 and 2); [2] to every context. Defaults 4, 4, 12. A value
+ * use 2 and 2, resp. 4 and 2); [2] to every context. Defaults 4, 4, 12;
+ * until a shape is set, small lists use 2 and 1 of [0] and [1]. A value
  * <= 0 keeps the current one; any other value outside the list is FQ_EINVAL
  * (nothing changes). Results do not depend on the shapes (tiles only
  * partition the work; every prefix crossing tiles is exact); only speed does.

@@ -366,6 +366,7 @@ struct fq_ctx {
     // sizes the next iteration is expected to have (those of the last one)
     int64_t spawn_hint = 0, main_hint = 0, att_hint = 0;
     Grids plan{};  // launch geometry of the blocks being enqueued (choose_plan)
+    bool tiles_set = false;  // the caller has chosen the tile shapes
     std::vector<double> shift;
     std::vector<int> vary;
     std::vector<int64_t> nprev;
@@ -530,12 +531,28 @@ Grids sized_grids(const fq_ctx *c, double room)
         return (int)std::max<int64_t>(1, std::min<int64_t>(cap, n));
     };
     const int64_t ns = c->spawn_hint, nm = c->main_hint + c->spawn_hint;
+    if (!c->tiles_set) {
+        // Tile shapes by size, unless the caller has set them. On a list of
+        // few tiles a thread's serial work is what counts (8-site ring, 4e3
+        // determinants: 108 us an iteration with four attempts and positions
+        // per thread, 92 with two and one; 14 electrons, 8e5 determinants: 194
+        // against 202 and 212). A molecular attempt is long, so less than two
+        // rounds of tiles leave many compute units idle in the second
+        // (1e6 determinants: 402 us, 383 with two attempts per thread).
+        // (A shape in use is kept a little beyond its line.)
+        const double few_m = c->plan.merge_i == 1 ? 40 : 32, few_s = c->plan.spawn_i == 2 ? 40 : 32;
+        const double rounds = c->plan.spawn_i == 2 ? 2.25 : 2.0;
+        if ((double)nm < few_m * 256 * g.merge_i) g.merge_i = 1;
+        if ((double)c->att_hint < few_s * SP_T * g.spawn_i ||
+            (c->kind == FQ_MOLECULAR && (double)c->att_hint < rounds * SP_T * g.spawn_i * g.spawn))
+            g.spawn_i = 2;
+    }
     g.part = fit(c->grids.part, c->att_hint / SPAN_MIN, 256);
-    g.spawn = fit(c->grids.spawn, c->att_hint, SP_T * (c->W <= 2 ? c->grids.spawn_i : 2));
-    g.sort = fit(c->grids.sort, ns, 256 * c->grids.sort_i);
+    g.spawn = fit(c->grids.spawn, c->att_hint, SP_T * (c->W <= 2 ? g.spawn_i : 2));
+    g.sort = fit(c->grids.sort, ns, 256 * g.sort_i);
     g.reduce = fit(c->grids.reduce, ns, 768);
-    g.merge = fit(c->grids.merge, nm, MERGE_TILE_MIN * (c->W <= 2 ? c->grids.merge_i : 2));
-    g.move = fit(c->grids.move, nm, MERGE_TILE_MIN * (c->W <= 2 ? c->grids.merge_i : 2));
+    g.merge = fit(c->grids.merge, nm, MERGE_TILE_MIN * (c->W <= 2 ? g.merge_i : 2));
+    g.move = fit(c->grids.move, nm, MERGE_TILE_MIN * (c->W <= 2 ? g.merge_i : 2));
     g.newdiag = fit(c->grids.newdiag, nm, 16384);
     // (about as many cluster selections as attempts; a block stages the prefix for a few passes)
     g.ccmc = fit(c->grids.ccmc, c->att_hint, 4 * 256);
@@ -1808,7 +1825,10 @@ fq_status fq_set_tiles(fq_ctx *c, const int32_t *tiles, int32_t n)
         if (tiles[i] > 0 && tiles[i] != ok[i][0] && tiles[i] != ok[i][1] && tiles[i] != ok[i][2])
             return fail(c, FQ_EINVAL, "tile shape not among the compiled variants");
     for (int i = 0; i < n && i < 3; ++i)
-        if (tiles[i] > 0) *dst[i] = tiles[i];
+        if (tiles[i] > 0) {
+            *dst[i] = tiles[i];
+            c->tiles_set = true;
+        }
     drop_graphs(c);
     return FQ_OK;
 }

@@ -285,7 +285,7 @@ __device__ __forceinline__ double eri_at(const DevSys &s, int p, int q, int r, i
 
 // packed plane-wave vectors: component c in bits [10c, 10c + 10), biased by 256;
 // sums and differences of a few vectors stay inside each 10-bit field
-__device__ __forceinline__ int pk_comp(int32_t v, int c) { return ((v >> (10 * c)) & 1023) - 256; }
+__host__ __device__ __forceinline__ int pk_comp(int32_t v, int c) { return ((v >> (10 * c)) & 1023) - 256; }
 __device__ __forceinline__ int pk_dn2(int32_t u, int32_t v)
 {
     const int dx = pk_comp(u, 0) - pk_comp(v, 0), dy = pk_comp(u, 1) - pk_comp(v, 1), dz = pk_comp(u, 2) - pk_comp(v, 2);

@@ -553,7 +553,21 @@ Grids sized_grids(const fq_ctx *c, double room)
     g.reduce = fit(c->grids.reduce, ns, 768);
     g.merge = fit(c->grids.merge, nm, MERGE_TILE_MIN * (c->W <= 2 ? g.merge_i : 2));
     g.move = fit(c->grids.move, nm, MERGE_TILE_MIN * (c->W <= 2 ? g.merge_i : 2));
-    g.newdiag = fit(c->grids.newdiag, nm, 16384);
+    // Chunks of the new determinants' diagonal. 16 density-matrix loops, 5e4
+    // pairs: 13.9 us with 16384 flags, 7.5 with 2048. Where a block stages
+    // tables short chunks cost as much as they bring (1e6 molecular
+    // determinants: 20 us with 16384, 21 with 4096, 23 with 2048; 7e7 of the
+    // 14-electron gas: 139 us with 16384, 163 with 8192).
+    {
+        const bool small = (double)nm < (c->plan.diag_chunk <= 4096 ? 2.2e6 : 2e6);
+        if (c->w.lds_list > 0)
+            g.diag_chunk = small ? 2048 : 8192;
+        else if (c->w.lds_diag > 0)
+            g.diag_chunk = small ? 4096 : 16384;
+        else
+            g.diag_chunk = small ? 2048 : 16384;
+    }
+    g.newdiag = fit(c->grids.newdiag, nm, g.diag_chunk);
     // (about as many cluster selections as attempts; a block stages the prefix for a few passes)
     g.ccmc = fit(c->grids.ccmc, c->att_hint, 4 * 256);
     g.ss = c->ss_active ? 1 : 0;
@@ -572,7 +586,7 @@ void choose_plan(fq_ctx *c)
                       within(g.spawn, lo.spawn, hi.spawn) && within(g.sort, lo.sort, hi.sort) &&
                       within(g.reduce, lo.reduce, hi.reduce) && within(g.merge, lo.merge, hi.merge) &&
                       within(g.newdiag, lo.newdiag, hi.newdiag) && within(g.ccmc, lo.ccmc, hi.ccmc) && g.spawn_i == lo.spawn_i &&
-                      g.merge_i == lo.merge_i && g.sort_i == lo.sort_i;
+                      g.merge_i == lo.merge_i && g.sort_i == lo.sort_i && g.diag_chunk == lo.diag_chunk;
     if (keep) return;
     c->w.sort_p = p;
     c->plan = sized_grids(c, 2.0);
@@ -1139,8 +1153,27 @@ fq_status init_system(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc, con
         const size_t m = (size_t)c->sys[0].n_spatial;
         size_t bytes = c->kind == FQ_UEG ? 8 * (m + m * m) : 8 * (m + 2 * m * m);
         // electron gas on a large basis: kinetic energies, v by |dn|^2, packed momenta
-        if (c->kind == FQ_UEG && bytes > (size_t)ND_LDS_MAX) bytes = 8 * m + 8 * (size_t)c->sys[0].vlen + 4 * m;
-        if (bytes <= (size_t)ND_LDS_MAX) w.lds_diag = (int32_t)bytes;
+        if (c->kind == FQ_UEG && bytes > (size_t)ND_LDS_MAX) {
+            bytes = 8 * m + 8 * (size_t)c->sys[0].vlen + 4 * m;
+            // electrons listed as bytes, plane waves as vectors of bytes
+            const HostSys &s0 = c->sys[0];
+            const size_t lists = 4 * (size_t)DIAG_T * ((s0.na + 3) / 4 + (s0.nb + 3) / 4);
+            int n2max = 0;
+            for (int32_t v : s0.npk) {
+                int n2 = 0;
+                for (int k = 0; k < 3; ++k) n2 += pk_comp(v, k) * pk_comp(v, k);
+                n2max = std::max(n2max, n2);
+            }
+            if (c->W > 2 && m <= 256 && lists <= (size_t)DIAG_LIST_MAX && n2max <= DIAG_N2_MAX) {
+                bytes = (bytes + 8 * m + 15) & ~(size_t)15;
+                w.lds_list = (int32_t)lists;
+            }
+        }
+        bytes = (bytes + 15) & ~(size_t)15;
+        if (bytes <= (size_t)ND_LDS_MAX)
+            w.lds_diag = (int32_t)bytes;
+        else
+            w.lds_list = 0;
     }
     // heat-bath pair weights (upper triangle) staged in LDS by the single-replica spawn kernel
     if (one_system && c->kind == FQ_MOLECULAR) {

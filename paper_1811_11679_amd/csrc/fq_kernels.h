@@ -100,6 +100,9 @@ constexpr int SPAN_MIN = 2 * SP_T;
 constexpr int PART_MAX_BLOCKS = 8192;
 // largest diagonal-table staging of the new-determinant kernel (bytes of LDS)
 constexpr int ND_LDS_MAX = 65536;
+// threads of its blocks, largest electron lists of a block (54 electrons: 28 KB)
+// and largest |n|^2 of a plane wave on them (bytes hold 2 n and |n|^2)
+constexpr int DIAG_T = 512, DIAG_LIST_MAX = 32768, DIAG_N2_MAX = 127;
 __host__ __device__ inline int acc_rows(int R) { return R < ACC_LDS_R ? R : ACC_LDS_R; }
 
 // order-preserving unsigned key of a double (larger value, larger key)
@@ -206,6 +209,7 @@ struct Work {
     int32_t tau_search;  // track the maxima of the time-step search (per replica)
     int32_t lds_tables;  // bytes of UEG tables the spawn kernel stages in LDS (0: read from global)
     int32_t lds_diag;    // bytes of diagonal tables the new-determinant kernel stages in LDS
+    int32_t lds_list;    // bytes of its threads' electron lists (0: none)
     // method: 0 FCIQMC; density matrices on pair keys (Sec. 2.3): 1 DMQMC
     // (both ends spawn, 2 attempts per walker unit), 2 IP-DMQMC (the ket end)
     int32_t dm;
@@ -232,6 +236,7 @@ struct Grids {
     int spawn_i = 4, merge_i = 4, sort_i = 12;
     int ccmc = 1024;  // blocks of the cluster-sampling kernel
     int ss = 0;       // the deterministic space is active
+    int diag_chunk = 16384;  // flags a block of the new-determinant diagonal kernel scans at once
 };
 
 // kernels of one iteration, in launch order (per-kernel timing slots; the

@@ -649,16 +649,77 @@ __global__ __launch_bounds__(MV_T) void k_move(Work w, int runs)
 // Each block scans a chunk of the new list, queues the marked entries in LDS
 // and evaluates them one per thread, so no lane idles on unmarked entries;
 // for a single replica the diagonal's tables are read from LDS.
-// Chunks of 16384 flags: new determinants are a few per cent of the list, and
-// a chunk must hold enough of them to fill the block's waves (at 4096 flags a
-// 256-thread block had about one partial wave of work per chunk)
-constexpr int ND_T = 512, ND_CHUNK = 16384;
-static_assert(ND_CHUNK == ND_T * 32, "each thread scans 32 new-determinant flags");
+// New determinants are a few per cent of the list: a chunk must hold enough of
+// them to fill the block's waves and to pay for its tables, and there must be
+// enough chunks for the compute units: 4, 8, 16 or 32 flags per thread by the
+// host's rule (Grids::diag_chunk).
+constexpr int ND_T = DIAG_T;
+
+// Diagonal of the electron gas on a large basis (its exchange table does not
+// fit LDS). A thread lists its electrons, alpha and beta, as bytes in LDS; the
+// exchange of a pair is v(|n_p - n_q|^2), the distance one dot product of bytes:
+// pa = (n_p, 1), pb = (-2 n_q, |n_q|^2), |n_p - n_q|^2 = pa . pb + |n_p|^2. The
+// terms are subtracted in the order of diag_ueg: rows P ascending (both spins),
+// Q > P of the same spin ascending. Bound: LDS reads (12 bytes a pair at
+// random). 54 electrons, 251
+// plane waves, 4.4e6 determinants: 353 -> 118 us; 123 plane waves 35 -> 21 us.
+struct DiagLists {
+    const double *eps, *vtab;
+    const int32_t *pa, *pb;
+    uint32_t *word;  // this thread's list: four electrons a word, ND_T words apart
+    int na, nb;
+
+    template <int W>
+    __device__ double operator()(const uint64_t (&key)[W]) const
+    {
+        const int wa = (na + 3) >> 2;
+        unsigned char *byte = (unsigned char *)word;
+        double e = 0.0;
+        int ia = 0, ib = 0;
+        for_bits<W>(key, [&](int P) {
+            e = e + eps[P >> 1];
+            const int k = (P & 1) ? 4 * wa + ib : ia;
+            byte[(size_t)(k >> 2) * (4 * ND_T) + (k & 3)] = (unsigned char)(P >> 1);
+            if (P & 1) ++ib; else ++ia;
+        });
+        auto at = [&](int k) -> int { return byte[(size_t)(k >> 2) * (4 * ND_T) + (k & 3)]; };
+        ia = ib = 0;
+        int ca = na > 0 ? at(0) : 0, cb = nb > 0 ? at(4 * wa) : 0;
+        for (int r = 0; r < na + nb; ++r) {
+            const bool alpha = ib >= nb || (ia < na && ca <= cb);  // 2a < 2b + 1
+            const int p = alpha ? ca : cb, k = alpha ? ia : ib, n = alpha ? na : nb;
+            const int w0 = alpha ? 0 : wa, wn = (n + 3) >> 2;
+            const int32_t vp = pa[p], np = pb[p] >> 24;
+            for (int w = (k + 1) >> 2; w < wn; ++w) {
+                const uint32_t q4 = word[(w0 + w) * ND_T];
+                double v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int i = 4 * w + j;
+                    const bool in = i > k && i < n;
+                    const int q = in ? (int)((q4 >> (8 * j)) & 255u) : p;
+                    v[j] = vtab[__builtin_amdgcn_sdot4(vp, pb[q], np, false)];
+                    v[j] = in ? v[j] : 0.0;
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) e = e - v[j];
+            }
+            if (alpha) {
+                ++ia;
+                ca = ia < na ? at(ia) : 0;
+            } else {
+                ++ib;
+                cb = ib < nb ? at(4 * wa + ib) : 0;
+            }
+        }
+        return e;
+    }
+};
 
 // The blocks beyond nd_blocks end the iteration, one replica each: the merge is
 // the last kernel that adds to the accumulators.
 template <int KIND, int W>
-__global__ __launch_bounds__(ND_T) void k_new_diag(Work w, int nd_blocks, int nb_red, int nb_mrg)
+__global__ __launch_bounds__(ND_T) void k_new_diag(Work w, int nd_blocks, int per, int nb_red, int nb_mrg)
 {
     const Ctl *c = w.ctl;
     if (c->err) return;
@@ -668,7 +729,7 @@ __global__ __launch_bounds__(ND_T) void k_new_diag(Work w, int nd_blocks, int nb
         return;
     }
     extern __shared__ __align__(16) unsigned char dyn_lds[];
-    __shared__ uint16_t s_q[ND_CHUNK];  // offsets of the chunk's new determinants
+    uint16_t *s_q = (uint16_t *)(dyn_lds + w.lds_diag + w.lds_list);  // offsets of the chunk's new determinants
     __shared__ int s_n;
     const long long n = c->n_main_new;
     const DevSys &s0 = w.sys[w.rep[0].sys];
@@ -676,6 +737,8 @@ __global__ __launch_bounds__(ND_T) void k_new_diag(Work w, int nd_blocks, int nb
     const bool local = w.lds_diag > 0 && (KIND == K_UEG || KIND == K_MOLECULAR);
     UegTables lu = s0.u;
     const double *lhd = s0.hd, *lJ = s0.Jt, *lK = s0.Kt;
+    DiagLists lists{};
+    constexpr bool LISTS = KIND == K_UEG && W > 2;
     if (local) {
         double *t0 = (double *)dyn_lds;
         const int m = s0.n_spatial;
@@ -699,6 +762,22 @@ __global__ __launch_bounds__(ND_T) void k_new_diag(Work w, int nd_blocks, int nb
                 lu.vtab = t1;
                 lu.npk = t2;
                 lu.vx = nullptr;
+                if (LISTS && w.lds_list > 0) {
+                    int32_t *pa = t2 + m, *pb = pa + m;
+                    for (int i = threadIdx.x; i < m; i += ND_T) {
+                        const int32_t n = s0.u.npk[i];
+                        const int x = pk_comp(n, 0), y = pk_comp(n, 1), z = pk_comp(n, 2);
+                        pa[i] = (x & 255) | (y & 255) << 8 | (z & 255) << 16 | 1 << 24;
+                        pb[i] = (-2 * x & 255) | (-2 * y & 255) << 8 | (-2 * z & 255) << 16 | (x * x + y * y + z * z) << 24;
+                    }
+                    lists.eps = t0;
+                    lists.vtab = t1;
+                    lists.pa = pa;
+                    lists.pb = pb;
+                    lists.word = (uint32_t *)(dyn_lds + w.lds_diag) + threadIdx.x;
+                    lists.na = s0.na;
+                    lists.nb = s0.nb;
+                }
             }
         } else {
             double *t1 = t0 + m, *t2 = t1 + m * m;
@@ -712,22 +791,32 @@ __global__ __launch_bounds__(ND_T) void k_new_diag(Work w, int nd_blocks, int nb
             lK = t2;
         }
     }
-    for (long long base = (long long)blockIdx.x * ND_CHUNK; base < n; base += (long long)nd_blocks * ND_CHUNK) {
+    const int chunk = ND_T * per;
+    for (long long base = (long long)blockIdx.x * chunk; base < n; base += (long long)nd_blocks * chunk) {
         if (threadIdx.x == 0) s_n = 0;
         __syncthreads();
-        // the merge's new-determinant flags, 32 per thread in two 16-byte loads
+        // the merge's new-determinant flags, 4 to 32 of a thread in one or two loads
         {
-            const int q0 = threadIdx.x * 32;
+            const int q0 = threadIdx.x * per;
             const long long i0 = base + q0;
-            if (i0 + 32 <= n) {
-                const uint4 f0 = *(const uint4 *)(w.newdet + i0);
-                const uint4 f1 = *(const uint4 *)(w.newdet + i0 + 16);
-                const uint32_t fw[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
+            if (i0 + per <= n) {
+                uint32_t fw[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+                if (per >= 16) {
+                    const uint4 f = *(const uint4 *)(w.newdet + i0);
+                    fw[0] = f.x, fw[1] = f.y, fw[2] = f.z, fw[3] = f.w;
+                    if (per == 32) {
+                        const uint4 g = *(const uint4 *)(w.newdet + i0 + 16);
+                        fw[4] = g.x, fw[5] = g.y, fw[6] = g.z, fw[7] = g.w;
+                    }
+                } else {
+                    fw[0] = *(const uint32_t *)(w.newdet + i0);
+                    if (per == 8) fw[1] = *(const uint32_t *)(w.newdet + i0 + 4);
+                }
 #pragma unroll
                 for (int b = 0; b < 32; ++b)
                     if ((fw[b >> 2] >> (8 * (b & 3))) & 0xFFu) s_q[atomicAdd(&s_n, 1)] = (uint16_t)(q0 + b);
             } else {
-                for (int b = 0; b < 32 && i0 + b < n; ++b)
+                for (int b = 0; b < per && i0 + b < n; ++b)
                     if (w.newdet[i0 + b]) s_q[atomicAdd(&s_n, 1)] = (uint16_t)(q0 + b);
             }
         }
@@ -740,7 +829,19 @@ __global__ __launch_bounds__(ND_T) void k_new_diag(Work w, int nd_blocks, int nb
             if (local) {
                 double e;
                 if constexpr (KIND == K_UEG) {
-                    e = diag_ueg<W>(lu, key);
+                    bool listed = false;
+                    if constexpr (LISTS) {
+                        // (an imported determinant may hold other numbers of electrons)
+                        int ca = 0, cb = 0;
+#pragma unroll
+                        for (int x = 0; x < W; ++x) {
+                            ca += __popcll(key[x] & 0x5555555555555555ull);
+                            cb += __popcll(key[x] & 0xAAAAAAAAAAAAAAAAull);
+                        }
+                        listed = w.lds_list > 0 && ca == s0.na && cb == s0.nb;
+                        if (listed) e = lists(key);
+                    }
+                    if (!listed) e = diag_ueg<W>(lu, key);
                 } else {
                     const int m = s0.n_spatial;
                     e = 0.0;
@@ -785,7 +886,8 @@ static void launch_merge_kind(int part, const Work &w, const Grids &g, hipStream
 {
     if (part == 2) {
         const int ends = w.ccmc_trunc > 0 ? 0 : w.R;  // CCMC ends after its pair sum
-        k_new_diag<KIND, W><<<g.newdiag + ends, ND_T, w.lds_diag, s>>>(w, g.newdiag, g.reduce, g.merge);
+        const int per = g.diag_chunk / ND_T, lds = w.lds_diag + w.lds_list + 2 * g.diag_chunk;
+        k_new_diag<KIND, W><<<g.newdiag + ends, ND_T, lds, s>>>(w, g.newdiag, per, g.reduce, g.merge);
         return;
     }
     const int mi = W <= 2 ? g.merge_i : 2;

@@ -5,6 +5,7 @@ table staged in LDS, and by the general loop beyond that (or with several
 different systems, which stage no table). Every list must equal the oracle's
 bit for bit.
 """
+import numpy as np
 import pytest
 
 from gpu_helpers import assert_same_estimators, assert_same_lists, gpu_context, oracle_qmc, oracle_system, say
@@ -31,4 +32,49 @@ def test_heat_bath_electrons(orbitals, up, down):
         assert_same_lists(ctx, run, where=f"{orbitals} orbitals block {blk}")
         assert_same_estimators(ctx.estimators(), run.estimators(), where=f"{orbitals} orbitals block {blk}")
     say(f"[case] {ctx.estimators()['n_occupied']} determinants, {ctx.estimators()['n_spawned']} spawned")
+    ctx.close()
+
+
+# the electron gas on bases whose exchange table does not fit LDS (more than 90
+# plane waves): electron lists as bytes, with numbers of electrons that fill and
+# do not fill a word of the list, none of one spin, and lists of several chunks
+@pytest.mark.parametrize("ecut,up,down,walkers", [(9, 7, 7, 1500), (9, 2, 1, 500), (9, 3, 0, 500), (9, 4, 5, 1500),
+                                                  (9, 8, 9, 500), (14, 27, 27, 100), (14, 30, 17, 100)])
+def test_diagonal_of_large_bases(ecut, up, down, walkers):
+    sysd = dict(kind="ueg", rs=1.0, ecut_n2=ecut, n_alpha=up, n_beta=down)
+    q = dict(workloads.UEG14["qmc"], tau=0.002 if up + down < 20 else 0.0002, init_pop=walkers,
+             target_population=4 * walkers)
+    say(f"[case] electron gas, cutoff {ecut}, {up}+{down} electrons")
+    ctx = gpu_context([sysd], [q], main_capacity=1 << 19, spawn_capacity=1 << 19)
+    run = O.Run(oracle_system(sysd), oracle_qmc(sysd, q))
+    for blk in range(3):
+        ctx.step(10)
+        run.step(10)
+        assert_same_lists(ctx, run, where=f"cutoff {ecut} block {blk}")
+        assert_same_estimators(ctx.estimators(), run.estimators(), where=f"cutoff {ecut} block {blk}")
+    say(f"[case] {ctx.estimators()['n_occupied']} determinants")
+    ctx.close()
+
+
+def test_diagonal_of_imported_electron_numbers():
+    """A list may be imported with determinants of other numbers of electrons
+    of a spin than the system has; what they spawn has them too."""
+    sysd = dict(kind="ueg", rs=1.0, ecut_n2=9, n_alpha=7, n_beta=7)
+    q = dict(workloads.UEG14["qmc"], init_pop=100.0, target_population=1e3)
+    ctx = gpu_context([sysd], [q], main_capacity=1 << 17, spawn_capacity=1 << 17)
+    run = O.Run(oracle_system(sysd), oracle_qmc(sysd, q))
+    keys, pops = run.export()
+    flipped = keys[0].copy()
+    low = int(flipped[0])
+    beta = next(b for b in range(1, 64, 2) if low >> b & 1)
+    alpha = next(b for b in range(0, 64, 2) if not low >> b & 1)
+    flipped[0] = np.uint64(low & ~(1 << beta) | (1 << alpha))
+    keys = np.concatenate([keys, flipped[None]])
+    pops = np.concatenate([pops, pops[:1]])
+    ctx.import_walkers(keys, pops)
+    run.import_walkers(keys, pops)
+    for blk in range(2):
+        ctx.step(10)
+        run.step(10)
+        assert_same_lists(ctx, run, where=f"block {blk}")
     ctx.close()

@@ -16,6 +16,7 @@
 #include <mutex>
 #include <numeric>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/fciqmc.h"
@@ -685,13 +686,58 @@ bool entry_less(const HostEntry &a, const HostEntry &b, int W)
     return key_cmp_host(a.key, b.key, W) < 0;
 }
 
-// initial estimators of each replica (iteration counter value, list as is)
-fq_status host_estimators(fq_ctx *c)
+// Sorts v; lists from SORT_PAR entries in parts by several threads, then merged
+// (1.4e5 rows of two key words: 10 ms by one thread). The caller's order leaves
+// no two entries equal that it could tell apart.
+constexpr size_t SORT_PAR = 1 << 14;
+template <typename T, typename Less>
+void sort_entries(std::vector<T> &v, Less less)
 {
-    std::vector<HostEntry> e;
-    int64_t n;
-    fq_status st = download_main(c, e, n);
-    if (st) return st;
+    const size_t n = v.size();
+    unsigned parts = 1;
+    while (n >= SORT_PAR && parts < 8 && 2 * parts <= std::thread::hardware_concurrency() && n / (2 * parts) >= SORT_PAR / 4)
+        parts *= 2;
+    if (parts < 2) {
+        std::sort(v.begin(), v.end(), less);
+        return;
+    }
+    std::vector<T> other(n);
+    auto bound = [&](unsigned p) { return n * p / parts; };
+    // runs job(0 .. count - 1), each but the first on a thread of its own (on this one if none can be had)
+    auto each = [&](unsigned count, auto &&job) {
+        std::vector<std::thread> th;
+        th.reserve(count);
+        for (unsigned p = 1; p < count; ++p) {
+            try {
+                th.emplace_back(job, p);
+            } catch (...) {  // no thread: the part is done here
+                job(p);
+            }
+        }
+        job(0);
+        for (auto &x : th) x.join();
+    };
+    each(parts, [&](unsigned p) { std::sort(v.begin() + bound(p), v.begin() + bound(p + 1), less); });
+    for (unsigned w = 1; w < parts; w *= 2) {
+        each(parts / (2 * w), [&](unsigned q) {
+            const size_t a = bound(2 * q * w), m = bound((2 * q + 1) * w), b = bound((2 * q + 2) * w);
+            std::merge(v.begin() + a, v.begin() + m, v.begin() + m, v.begin() + b, other.begin() + a, less);
+        });
+        v.swap(other);
+    }
+}
+
+// initial estimators of each replica (iteration counter value, list as is);
+// held: the list where the caller has it
+fq_status host_estimators(fq_ctx *c, const std::vector<HostEntry> *held = nullptr)
+{
+    std::vector<HostEntry> got;
+    if (!held) {
+        int64_t n;
+        fq_status st = download_main(c, got, n);
+        if (st) return st;
+    }
+    const std::vector<HostEntry> &e = held ? *held : got;
     for (int r = 0; r < c->R; ++r) {
         EstAcc a;
         std::memset(&a, 0, sizeof(a));
@@ -1591,7 +1637,7 @@ void sort_rows(const std::vector<uint64_t> &kk, const std::vector<int32_t> &pp, 
         for (int q = 0; q < W; ++q) rows[i].k[q] = kk[(size_t)q * n + i];
         rows[i].pop = pp[i];
     }
-    std::sort(rows.begin(), rows.end(), [](const Row &a, const Row &b) {
+    sort_entries(rows, [](const Row &a, const Row &b) {
         for (int q = W - 1; q >= 0; --q)
             if (a.k[q] != b.k[q]) return a.k[q] < b.k[q];
         return false;
@@ -1644,16 +1690,19 @@ fq_status fq_import_walkers(fq_ctx *c, int32_t instance, const uint64_t *keys, c
 {
     if (!c || instance < 0 || instance >= c->R || n < 0 || (n > 0 && (!keys || !pops)) || iteration < 0)
         return FQ_EINVAL;
-    std::vector<HostEntry> e;
-    int64_t m;
-    fq_status st = download_main(c, e, m);
-    if (st) return st;
-    std::vector<HostEntry> out;
-    for (const HostEntry &x : e) {
-        const uint32_t rep = c->rb ? (uint32_t)(x.skey >> (64 - c->rb)) : 0u;
-        if ((int)rep != instance) out.push_back(x);
+    fq_status st;
+    std::vector<HostEntry> out;  // the other instances' entries
+    if (c->R > 1) {
+        std::vector<HostEntry> e;
+        int64_t m;
+        if ((st = download_main(c, e, m))) return st;
+        for (const HostEntry &x : e) {
+            const uint32_t rep = c->rb ? (uint32_t)(x.skey >> (64 - c->rb)) : 0u;
+            if ((int)rep != instance) out.push_back(x);
+        }
     }
     std::vector<HostEntry> add;
+    add.reserve((size_t)n);
     for (int64_t i = 0; i < n; ++i) {
         if (pops[i] == 0) continue;
         HostEntry x;
@@ -1670,13 +1719,36 @@ fq_status fq_import_walkers(fq_ctx *c, int32_t instance, const uint64_t *keys, c
         x.dslot = -1;
         add.push_back(x);
     }
-    std::sort(add.begin(), add.end(), [&](const HostEntry &a, const HostEntry &b) { return entry_less(a, b, c->W); });
+    // sorted by place: an entry is moved once
+    {
+        struct Place {
+            uint64_t skey;
+            size_t i;
+        };
+        std::vector<Place> order(add.size());
+        for (size_t i = 0; i < add.size(); ++i) order[i] = Place{add[i].skey, i};
+        const int W = c->W;
+        sort_entries(order, [&add, W](const Place &a, const Place &b) {
+            if (a.skey != b.skey) return a.skey < b.skey;
+            return key_cmp_host(add[a.i].key, add[b.i].key, W) < 0;
+        });
+        std::vector<HostEntry> sorted(add.size());
+        for (size_t i = 0; i < add.size(); ++i) sorted[i] = add[order[i].i];
+        add.swap(sorted);
+    }
     for (size_t i = 1; i < add.size(); ++i)
         if (add[i].skey == add[i - 1].skey && key_cmp_host(add[i].key, add[i - 1].key, c->W) == 0)
             return fail(c, FQ_EINVAL, "duplicate determinant in import");
-    out.insert(out.end(), add.begin(), add.end());
     for (auto &x : out) x.dslot = -1;
-    std::sort(out.begin(), out.end(), [&](const HostEntry &a, const HostEntry &b) { return entry_less(a, b, c->W); });
+    // (one instance: its entries are the list; others are sorted already)
+    if (out.empty()) {
+        out.swap(add);
+    } else {
+        std::vector<HostEntry> all(out.size() + add.size());
+        std::merge(out.begin(), out.end(), add.begin(), add.end(), all.begin(),
+                   [&](const HostEntry &a, const HostEntry &b) { return entry_less(a, b, c->W); });
+        out.swap(all);
+    }
     c->shift[instance] = shift;
     c->vary[instance] = vary_shift;
     c->nprev[instance] = n_prev;
@@ -1692,7 +1764,7 @@ fq_status fq_import_walkers(fq_ctx *c, int32_t instance, const uint64_t *keys, c
     HIPCHK(c, h2d(c->stream, c->w.shift, c->h_shift, 8 * c->R));
     st = upload_main(c, out);
     if (st) return st;
-    st = host_estimators(c);
+    st = host_estimators(c, &out);
     if (st) return st;
     if (c->has_ss && c->t >= c->ss.start_iteration) return select_detspace(c);
     return FQ_OK;

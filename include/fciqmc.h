@@ -248,7 +248,7 @@ fq_status fq_init_system(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc,
  * fq_init_system. The array keeps the contents of the last context; every part
  * that must start at zero is cleared by this call. fq_destroy gives the array
  * back. */
-#define FQ_STATIC_WORKSPACE_BYTES (16u << 20)
+#define FQ_STATIC_WORKSPACE_BYTES (18u << 20)
 fq_status fq_init_system_static(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc,
                                 const fq_semistoch *ss, int32_t n_instances, int64_t main_capacity,
                                 int64_t spawn_capacity, void *hip_stream);

@@ -231,7 +231,7 @@ struct Layout {
     size_t total = 0;
     size_t ctl, acc, hist, shift, rep, sys, tables, att, span, mpart, mtile, mrun, mpop, msrc, st_scan, st_sort;
     size_t part_red, part_mrg, newdet;
-    size_t main[2][6];
+    size_t main[2][5];
     size_t sp[7];
     size_t u[4];
     size_t ds[14];
@@ -305,7 +305,6 @@ Layout make_layout(int R, int W, int64_t mcap, int64_t scap, int64_t tables, int
         L.main[b][2] = take(4 * (size_t)mcap);
         L.main[b][3] = take(8 * (size_t)mcap);
         L.main[b][4] = take(4 * (size_t)mcap);
-        L.main[b][5] = take(4 * (size_t)mcap);
     }
     L.sp[0] = take(8 * (size_t)scap);
     L.sp[1] = take(8 * (size_t)scap * (W + 1));
@@ -488,7 +487,8 @@ void set_main_views(fq_ctx *c)
         m.pop = (int32_t *)(c->ws + c->L.main[b][2]);
         m.kdiag = (double *)(c->ws + c->L.main[b][3]);
         m.dslot = (int32_t *)(c->ws + c->L.main[b][4]);
-        m.natt = (int32_t *)(c->ws + c->L.main[b][5]);
+        // attempt counts are needed at set-up only: they share the merge's populations
+        m.natt = (int32_t *)(c->ws + c->L.mpop);
     }
     c->w.cur = c->buf[c->cur];
     c->w.nxt = c->buf[c->cur ^ 1];

@@ -568,7 +568,8 @@ __device__ bool gen_ueg(const UegTables &s, const uint64_t (&D)[W], uint32_t w0,
         A = (int)pick(w1, (uint32_t)(2 * M));
     const int sA = A & 1, sB = sP + sQ - sA;
     const int p = P >> 1, q = Q >> 1, a = A >> 1;
-    const int32_t bp = s.npk[p] + s.npk[q] - s.npk[a];
+    const int32_t np = s.npk[p], nq = s.npk[q], na = s.npk[a];
+    const int32_t bp = np + nq - na;
     const int bx = pk_comp(bp, 0), by = pk_comp(bp, 1), bz = pk_comp(bp, 2);
     const int g = s.gmax;
     if (bx < -g || bx > g || by < -g || by > g || bz < -g || bz > g) return false;
@@ -584,14 +585,19 @@ __device__ bool gen_ueg(const UegTables &s, const uint64_t (&D)[W], uint32_t w0,
     flipbit<W>(child, lo);
     flipbit<W>(child, hi);
     pgen = sP == sQ ? s.pgen_same : s.pgen_opp;  // 2 / (C(N,2) n_A), n_A = M or 2M
-    uint64_t tmp[W];
+    // The sign of P -> lo, then Q -> hi: (-1) to the occupied orbitals between
+    // the ends, which the ranks i, j of P < Q and those of lo < hi give; the
+    // ranks of lo and hi only enter as their difference, so one count of the
+    // electrons in [lo, hi) replaces two counts and two moves.
+    int odd = i + j + (lo > P) + (hi > P) + (lo < Q) + (hi > Q);
 #pragma unroll
-    for (int t2 = 0; t2 < W; ++t2) tmp[t2] = D[t2];
-    const double s1 = parity_between<W>(tmp, P, lo);
-    flipbit<W>(tmp, P);
-    flipbit<W>(tmp, lo);
-    const double s2 = parity_between<W>(tmp, Q, hi);
-    h = (s1 * s2) * antisym_ueg(s, lo, hi, P, Q);
+    for (int t = 0; t < W; ++t) odd += __popcll(D[t] & range_mask(t, lo, hi));
+    // <lo hi|PQ> - <lo hi|QP>; momentum is conserved by the choice of B, whose vector is bp
+    const int32_t nl = A < B ? na : bp;
+    const int sl = lo & 1, sh = hi & 1;
+    const double x = (sl == sP && sh == sQ) ? s.vtab[pk_dn2(np, nl)] : 0.0;
+    const double y = (sl == sQ && sh == sP) ? s.vtab[pk_dn2(nq, nl)] : 0.0;
+    h = ((odd & 1) ? -1.0 : 1.0) * (x - y);
     return true;
 }
 

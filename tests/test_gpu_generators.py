@@ -78,3 +78,22 @@ def test_diagonal_of_imported_electron_numbers():
         run.step(10)
         assert_same_lists(ctx, run, where=f"block {blk}")
     ctx.close()
+
+
+# the exact projection's sums, in FP64 while the terms are small and by limbs
+# where they are not: populations below and above 2^28 units times the hopping
+@pytest.mark.parametrize("walkers", [50.0, 2e5, 1e6])
+def test_exact_projection_of_large_populations(walkers):
+    sysd = dict(kind="hubbard", n_sites=6, periodic=1, t=1.0, U=4.0, n_alpha=3, n_beta=3)
+    q = dict(workloads.HUBBARD8["qmc"], tau=0.001, init_pop=walkers, target_population=4 * walkers,
+             fixed_point_bits=10, spawn_cutoff=0.01, initial_shift=0.0)
+    ss = dict(size=7, start_iteration=5)
+    say(f"[case] ring of six, {walkers:g} walkers, deterministic space of 7")
+    ctx = gpu_context([sysd], [q], ss=ss, main_capacity=1 << 14, spawn_capacity=1 << 21)
+    run = O.Run(oracle_system(sysd), oracle_qmc(sysd, q, ss=ss))
+    for blk in range(3):
+        ctx.step(5)
+        run.step(5)
+        assert_same_lists(ctx, run, where=f"{walkers:g} walkers block {blk}")
+        assert_same_estimators(ctx.estimators(), run.estimators(), where=f"{walkers:g} walkers block {blk}")
+    ctx.close()

@@ -37,7 +37,7 @@ METRIC = "walker updates/s per FCIQMC iteration, plain vs batched; annihilation 
 HBM_PEAK_GBS = 8000.0
 
 
-def algorithmic_bytes(hist_prev, hist, W, ds_active=False, instances=1, ccmc=None):
+def algorithmic_bytes(hist_prev, hist, W, ds_active=False, instances=1, ccmc=None, passes=8):
     """Bytes each kernel must move per iteration (reads + writes of the data it
     owns). The deterministic slot of a main entry (4 bytes) is read and written
     only while a deterministic space is active; its sort key (8 bytes) is
@@ -52,10 +52,10 @@ def algorithmic_bytes(hist_prev, hist, W, ds_active=False, instances=1, ccmc=Non
     # spawn: parent key, sort key, population, slot and attempt offset read;
     # per spawn its sort key and record (key words, amplitude | initiator flag)
     out["spawn"] = nm * (kb + sk + 4 + ds + 8) + ns * (8 + kb + 8)
+    # radix passes over the top digits: as many as the plan makes (`passes`)
     out["sort_pass0"] = ns * (8 + 8 + 4)
-    for p in range(1, 8):
+    for p in range(1, passes):
         out[f"sort_pass{p}"] = ns * (8 + 4) * 2
-    out["sort_hist"] = ns * 8
     out["reduce"] = ns * (8 + 4 + kb + 8) + nu * (8 + kb + 8 + 4)
     # output: skey, key, pop, kdiag, slot, attempt offset and the new-determinant flag
     out["merge"] = nm * (sk + kb + 4 + 8 + ds) + nu * (8 + kb + 8 + 4) + nm2 * (sk + kb + 4 + 8 + ds + 8 + 1)
@@ -515,12 +515,14 @@ def run_single(args):
     ds_active = spec["ss"] is not None
     is_cc = q.get("method", 0) == F.CCMC
     cc = (q["ccmc_truncation"], s["n_alpha"] + s["n_beta"], q["fixed_point_bits"]) if is_cc else None
+    # slots of passes the plan does not make hold the time between two events, as "sort_hist" does
+    passes = max(1, sum(ktimes[f"sort_pass{p}"] > 2.0 * ktimes["sort_hist"] for p in range(8)))
     tot_bytes = {}
     for a, b in zip(prevk, hk):
-        for k, v in algorithmic_bytes(a, b, ctx.W, ds_active=ds_active, ccmc=cc).items():
+        for k, v in algorithmic_bytes(a, b, ctx.W, ds_active=ds_active, ccmc=cc, passes=passes).items():
             tot_bytes[k] = tot_bytes.get(k, 0) + v
     cand = {"spawn": ["spawn"], "merge": ["merge"], "reduce": ["reduce"], "new_diag": ["new_diag"],
-            "sort_pass": [f"sort_pass{p}" for p in range(8)]}
+            "sort_pass": [f"sort_pass{p}" for p in range(passes)]}
     if is_cc:
         # the cluster slot holds the prefix scan and the cluster sampler (two launches)
         cand["ccmc_clusters"] = ["ccmc_clusters"]

@@ -722,7 +722,10 @@ __device__ bool gen_heatbath(const DevSys &s, double p_single, const uint64_t (&
     double T = 0.0;
     int Ps = -1, Qs = -1;
     U4 r1;
-    if (stri && N <= HB_ROWS) {
+    int held = 0;  // (an imported determinant may hold another number of electrons)
+#pragma unroll
+    for (int i = 0; i < W; ++i) held += __popcll(D[i]);
+    if (stri && N <= HB_ROWS && held == N) {
         PairSums sums;
         sums.total<W>(stri, nso, N, D);
         T = sums.T;

@@ -80,6 +80,29 @@ def test_diagonal_of_imported_electron_numbers():
     ctx.close()
 
 
+def test_heat_bath_of_imported_electron_numbers():
+    """The same for the heat-bath generator, with one electron more: the general
+    loops, which an instance beside one of another system takes, are the reference."""
+    ints = synth.molecular_integrals(8)
+    sysd = dict(kind="molecular", n_alpha=3, n_beta=3)
+    q = dict(workloads.MOL30["qmc"], tau=0.005, init_pop=200.0, target_population=2e3)
+    lists = []
+    for others in ([], [dict(sysd, n_beta=2)]):
+        n = 1 + len(others)
+        ctx = gpu_context([sysd] + others, [q] * n, ints=ints, replicas=list(range(n)), main_capacity=1 << 16,
+                          spawn_capacity=1 << 16)
+        keys, pops = ctx.export(0)
+        more = keys[0].copy()
+        more[0] |= np.uint64(1 << next(b for b in range(16) if not int(more[0]) >> b & 1))
+        ctx.import_walkers(np.concatenate([keys, more[None]]), np.concatenate([pops, pops[:1]]))
+        ctx.step(20)
+        lists.append(ctx.export(0))
+        ctx.close()
+    for one, other in zip(*lists):
+        assert np.array_equal(one, other)
+    assert len(lists[0][0]) > 100
+
+
 # the exact projection's sums, in FP64 while the terms are small and by limbs
 # where they are not: populations below and above 2^28 units times the hopping
 @pytest.mark.parametrize("walkers", [50.0, 2e5, 1e6])

@@ -20,7 +20,7 @@
 // records on one sort key with different determinants (hash collisions) are
 // put in full order by a rare last step.
 //
-// Bound: the gathers of the records (8W + 8 bytes at random). The one to three
+// Bound: the gathers of the records (8W + 8 bytes at random). The one to four
 // radix passes and this kernel replace eight passes, a reduction, its
 // collision fix-up and a repeated reduction: each launch costs about 4.5 us in
 // a replayed graph however little it does, and each pass a trip over the list.

@@ -1433,7 +1433,7 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
         HIPCHK(c, hipStreamSynchronize(c->stream));
         if (c->timing) {
             // stage boundaries in the launch order: scan+partition, spawn, sort
-            // (histogram + 8 passes), reduce (2 passes + fix-up), projection, merge
+            // (its passes), reduce, projection, merge
             static const int stage_of[N_KERNEL_SLOTS] = {0, 0, 1, 1, 2, 2, 2, 2, 2, 2, 2, 2, 2, 3, 3, 3, 5, 5, 5, 4, 4, 4, 4, 4};
             for (int k = 0; k < nb; ++k) {
                 hipEvent_t *e = &evs[(size_t)k * NE];

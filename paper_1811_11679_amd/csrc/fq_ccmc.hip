@@ -251,8 +251,11 @@ __global__ __launch_bounds__(CC_T) void k_ccmc_clusters(Work w)
     __syncthreads();
     const long long *cum = staged ? s_cum : w.ccmc_cum;
     const uint16_t *guide = staged ? s_guide : nullptr;
-    // may selection sel write a record?
+    // may selection sel write a record? (An imported list may hold excitors that
+    // add or remove electrons: the bounds below do not hold for those, so every
+    // selection is evaluated.)
     auto may_write = [&](long long sel) -> bool {
+        if (!w.ccmc_even) return true;
         const int sz = cluster_size(draw(TAG_CLUSTER, 0, t, (uint64_t)sel, k0, k1), smax);
         uint64_t hall[W], pall[W];
 #pragma unroll

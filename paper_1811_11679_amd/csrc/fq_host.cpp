@@ -1074,6 +1074,7 @@ fq_status init_system(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc, con
     w.tau_search = c->qmc[0].tau_search;
     w.dm = dm_method(c->method) ? c->method : 0;
     w.ccmc_trunc = c->method == FQ_CCMC ? c->qmc[0].ccmc_truncation : 0;
+    w.ccmc_even = 1;
     w.single_cap = (int32_t)singles;
     w.ccmc_cum = (long long *)(c->ws + c->L.cc_cum);
     w.st_ccmc = (unsigned long long *)(c->ws + c->L.st_ccmc);
@@ -1703,6 +1704,7 @@ fq_status fq_import_walkers(fq_ctx *c, int32_t instance, const uint64_t *keys, c
     }
     std::vector<HostEntry> add;
     add.reserve((size_t)n);
+    bool even = true;  // CCMC: every excitor has as many particles as holes
     for (int64_t i = 0; i < n; ++i) {
         if (pops[i] == 0) continue;
         HostEntry x;
@@ -1710,9 +1712,13 @@ fq_status fq_import_walkers(fq_ctx *c, int32_t instance, const uint64_t *keys, c
         for (int q = 0; q < c->W; ++q) x.key[q] = keys[(size_t)i * c->W + q];
         if (c->method == FQ_CCMC) {
             // CCMC: no amplitude beyond the truncation level
-            int d = 0;
-            for (int q = 0; q < c->W; ++q) d += __builtin_popcountll(x.key[q] ^ c->sys[instance].ref[q]);
+            int d = 0, more = 0;
+            for (int q = 0; q < c->W; ++q) {
+                d += __builtin_popcountll(x.key[q] ^ c->sys[instance].ref[q]);
+                more += __builtin_popcountll(x.key[q]) - __builtin_popcountll(c->sys[instance].ref[q]);
+            }
             if (d / 2 > c->qmc[0].ccmc_truncation) return fail(c, FQ_EINVAL, "excitor beyond the truncation level");
+            even = even && more == 0;
         }
         x.skey = host_skey(host_hash(x.key, c->W) & c->hmask, (uint32_t)instance, c->rb);
         x.pop = pops[i];
@@ -1760,6 +1766,7 @@ fq_status fq_import_walkers(fq_ctx *c, int32_t instance, const uint64_t *keys, c
     ctl.ss_active = 0;
     HIPCHK(c, h2d(c->stream, c->w.ctl, &ctl, sizeof(Ctl)));
     c->ss_active = false;
+    c->w.ccmc_even = even ? 1 : 0;  // (upload_main drops the captured graphs)
     for (int r = 0; r < c->R; ++r) c->h_shift[r] = c->shift[r];
     HIPCHK(c, h2d(c->stream, c->w.shift, c->h_shift, 8 * c->R));
     st = upload_main(c, out);

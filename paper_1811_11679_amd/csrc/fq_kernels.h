@@ -217,6 +217,7 @@ struct Work {
     // exclusive prefix of |N_i| over the current list (reference masked),
     // its look-back status words and the queue of singles of the new list
     int32_t ccmc_trunc;
+    int32_t ccmc_even;          // every excitor has as many particles as holes
     int32_t single_cap;
     long long *ccmc_cum;        // [main_cap + 1]
     unsigned long long *st_ccmc;

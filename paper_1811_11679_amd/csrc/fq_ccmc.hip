@@ -202,10 +202,11 @@ template <int KIND, int W>
 __global__ __launch_bounds__(CC_T) void k_ccmc_clusters(Work w)
 {
     Ctl *c = w.ctl;
-    if (c->err) return;
     const RepParams &rp = w.rep[0];
     const DevSys &sy = w.sys[rp.sys];
-    const long long n0 = c->ccmc_n0, nex = c->ccmc_nex;
+    const long long n0 = c->ccmc_n0, nex = c->ccmc_nex, n = c->n_main;
+    const uint32_t t = c->t;
+    if (block_stops(c)) return;
     if (n0 == 0) {
         if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&c->err, ERR_NOREF);
         return;
@@ -215,8 +216,6 @@ __global__ __launch_bounds__(CC_T) void k_ccmc_clusters(Work w)
     const int bits = rp.bits;
     const long long nc = bits ? (nex + (1ll << bits) - 1) >> bits : nex;
     if (smax < 2 || nc == 0) return;
-    const long long n = c->n_main;
-    const uint32_t t = c->t;
     const uint32_t k0 = rp.k0, k1 = rp.k1 ^ 0x80000000u;
     const double an0 = (double)(n0 < 0 ? -n0 : n0);
     const double S = w.shift[0];

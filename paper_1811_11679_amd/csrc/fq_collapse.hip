@@ -121,7 +121,6 @@ __global__ __launch_bounds__(CL_T, 4) void k_collapse(Work w, const uint64_t *sk
                                                    int passes)
 {
     Ctl *c = w.ctl;
-    if (c->err) return;
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     long long *tab = (long long *)dyn_lds;  // estimator table, acc_rows(R) rows
     const int rl = acc_rows(w.R);
@@ -142,6 +141,7 @@ __global__ __launch_bounds__(CL_T, 4) void k_collapse(Work w, const uint64_t *sk
     const long long ntiles = (n + CL_SPAN - 1) / CL_SPAN;
     const int sh = 64 - 8 * passes;
     const int tid = threadIdx.x;
+    if (block_stops(c)) return;
     long long a_n = 0, a_sum = 0, a_uniq = 0;  // this thread's estimator sums of replica a_rep
     int a_rep = -1;
     auto acc_flush = [&]() {

@@ -422,7 +422,8 @@ __global__ __launch_bounds__(64 * DP_WAVES) void k_det_project_split(Work w)
     // space: the columns are 16 replicas, one K_DD for all. Otherwise: one
     // replica per job, in column 0.
     const Ctl *c = w.ctl;
-    if (c->err || !c->ss_active || w.ds.precision != 1) return;
+    const bool ss = c->ss_active != 0 && w.ds.precision == 1;
+    if (block_stops(c) || !ss) return;
     __shared__ float s_part[DP_WAVES][64][4];
     const int n = w.ds.n, np = w.ds.npad;
     const int lane = lane_id(), wv = threadIdx.x >> 6;

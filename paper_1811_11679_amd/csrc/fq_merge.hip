@@ -250,7 +250,6 @@ template <int KIND, int W, bool MULTI, int MI>
 __global__ __launch_bounds__((MergeCfg<W, MI>::T), (MergeCfg<W, MI>::WPE)) void k_merge(Work w)
 {
     Ctl *c = w.ctl;
-    if (c->err) return;
     constexpr int MG_T = MergeCfg<W, MI>::T, TILE = MergeCfg<W, MI>::TILE;
     __shared__ uint64_t s_sk[TILE];            // sort keys by slot
     constexpr int CHUNK = 64;                  // tiles whose splits are found at once
@@ -267,6 +266,7 @@ __global__ __launch_bounds__((MergeCfg<W, MI>::T), (MergeCfg<W, MI>::WPE)) void 
     const uint32_t t = c->t;
     const bool ss = c->ss_active != 0;
     const int tid = threadIdx.x;
+    if (block_stops(c)) return;
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     long long *tab = (long long *)dyn_lds;  // estimator table, acc_rows(R) rows
     const int rl = acc_rows(w.R);
@@ -523,7 +523,6 @@ template <int W, bool MULTI, int MI>
 __global__ __launch_bounds__(MV_T) void k_move(Work w, int runs)
 {
     Ctl *c = w.ctl;
-    if (c->err) return;
     constexpr int TILE = MergeCfg<W, MI>::TILE, WAVES = MV_T / 64;
     static_assert(TILE == MV_T * MI, "a thread takes MI positions");
     __shared__ long long s_w[WAVES];
@@ -534,6 +533,7 @@ __global__ __launch_bounds__(MV_T) void k_move(Work w, int runs)
     const long long ntiles = (na + nb + TILE - 1) / TILE;
     const long long run = (ntiles + runs - 1) / runs, per = (ntiles + gridDim.x - 1) / gridDim.x;
     const long long t0 = min((long long)blockIdx.x * per, ntiles), t1 = min(t0 + per, ntiles);
+    if (block_stops(c)) return;
     if (ntiles == 0 && blockIdx.x == 0 && tid == 0) {
         c->n_main_new = 0;
         w.att_off[0] = 0;

@@ -35,6 +35,21 @@ __device__ __forceinline__ unsigned long long st_load(unsigned long long *p)
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 __device__ __forceinline__ uint64_t lanemask_lt() { return (1ull << lane_id()) - 1ull; }
 
+// Whether an error bit is set, the same answer for every wave of the block. The
+// blocks of a launch set bits while others of it start: waves that each looked
+// for themselves could disagree, and the rest of a block would go on without
+// the wave that keeps its loop counts, splits or sums. Called once by every
+// thread, after the kernel has read its sizes, which then are on their way
+// together with the bits (one after the other cost the eight-site ring 1.4 us
+// of 92 an iteration).
+__device__ __forceinline__ bool block_stops(const Ctl *c)
+{
+    __shared__ uint32_t s_err;
+    if (threadIdx.x == 0) s_err = c->err;
+    __syncthreads();
+    return s_err != 0;
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v)
 {

@@ -76,7 +76,6 @@ template <int KIND, int W, bool MULTI, bool LT, int SP_I>
 __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
 {
     Ctl *c = w.ctl;
-    if (c->err) return;
     constexpr int SPAN = SP_T * SP_I;
     constexpr int LCAP = SPAN + 2;
     __shared__ long long s_off[LCAP];
@@ -90,9 +89,9 @@ __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
     for (int i = threadIdx.x; i < w.sort_p * 256; i += SP_T) (&s_hist[0][0])[i] = 0;
     const long long total = c->n_att;
     const long long nspans = (total + SPAN - 1) / SPAN;
-    if (nspans + 1 > w.span_cap) return;
     const uint32_t t = c->t;
     const bool ss = c->ss_active != 0;
+    if (block_stops(c) || nspans + 1 > w.span_cap) return;
     const int lane = lane_id(), wid = threadIdx.x >> 6;
     // time-step search: the largest |H_ji| / p_gen of this thread's attempts
     // of replica rs_rep

@@ -1,0 +1,83 @@
+"""Errors that the blocks of a running kernel raise: the call fails, and the list
+is the failing iteration's input."""
+import numpy as np
+import pytest
+
+from gpu_helpers import assert_same_lists, gpu_context, oracle_qmc, oracle_system, say
+from oracle import oracle as O
+from paper_1811_11679_amd import fciqmc as F
+from paper_1811_11679_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def _fails(ctx, code, times=3):
+    """the step fails with this code each time and leaves list and counter as they were"""
+    with pytest.raises(F.FqError) as ei:
+        ctx.step(100)
+    assert ei.value.code == code, ei.value
+    keys, pops = ctx.export()
+    at = ctx.estimators()["iteration"]
+    for _ in range(times):
+        with pytest.raises(F.FqError) as ei:
+            ctx.step(1)
+        assert ei.value.code == code, ei.value
+        k, p = ctx.export()
+        assert np.array_equal(k, keys) and np.array_equal(p, pops)
+        assert ctx.estimators()["iteration"] == at
+    return at
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("main,spawn", [(1 << 18, 6000), (1 << 15, 1 << 17)])
+def test_list_capacities(main, spawn, graph):
+    sysd, w = workloads.UEG14["system"], workloads.UEG14["qmc"]
+    q = dict(w, init_pop=5e3, target_population=2e4)
+    say(f"[case] electron gas into capacities {main} and {spawn}, graph={graph}")
+    ctx = gpu_context([sysd], [q], main_capacity=main, spawn_capacity=spawn, graph=graph)
+    at = _fails(ctx, F.FQ_ECAPACITY)
+    assert at > 3
+    run = O.Run(oracle_system(sysd), oracle_qmc(sysd, q))
+    run.step(at)
+    assert_same_lists(ctx, run, where=f"before the failing iteration {at + 1}")
+    ctx.close()
+
+
+def test_cluster_records_beyond_the_spawn_capacity():
+    s, q = workloads.UEG14_CCSD["system"], dict(workloads.UEG14_CCSD["qmc"], init_pop=2e4, target_population=1e9)
+    say("[case] CCSD on the 14-electron gas, room for half of the clusters' records")
+    ctx = gpu_context([s], [q], main_capacity=1 << 14, spawn_capacity=1 << 20)
+    ctx.step(60)
+    keys, pops = ctx.export()
+    ctx.step(1)
+    e = ctx.estimators()
+    ctx.close()
+    assert e["n_cluster_spawns"] > 2
+    room = e["n_spawned"] - e["n_cluster_spawns"] // 2
+    ctx = gpu_context([s], [q], main_capacity=1 << 14, spawn_capacity=room)
+    ctx.import_walkers(keys, pops, iteration=60)
+    _fails(ctx, F.FQ_ECAPACITY, times=5)
+    for got, want in zip(ctx.export(), (keys, pops)):
+        assert np.array_equal(got, want)
+    ctx.close()
+
+
+def test_populations_beyond_their_range():
+    """Every entry of the list overflows in the merge, in all of its blocks at once."""
+    sysd = dict(kind="ueg", rs=1.0, ecut_n2=3, n_alpha=7, n_beta=7)
+    q = dict(workloads.UEG14["qmc"], tau=1e-6, init_pop=1.0, target_population=1e12, fixed_point_bits=20,
+             spawn_cutoff=0.5)
+    rng = np.random.default_rng(3)
+    dets = set()
+    while len(dets) < 20000:
+        up, down = rng.choice(27, 7, replace=False), rng.choice(27, 7, replace=False)
+        dets.add(sum(1 << 2 * int(b) for b in up) + sum(1 << 2 * int(b) + 1 for b in down))
+    keys = np.array(sorted(dets), np.uint64)[:, None]
+    pops = rng.choice(np.array([-1, 1], np.int32), len(keys)) * np.int32(2147483000)
+    say("[case] 20000 determinants at the end of the population range, growing")
+    ctx = gpu_context([sysd], [q], main_capacity=1 << 21, spawn_capacity=1 << 21)
+    ctx.import_walkers(keys, pops, shift=1000.0)
+    _fails(ctx, F.FQ_EOVERFLOW, times=5)
+    for got, want in zip(ctx.export(), (keys, pops)):
+        assert np.array_equal(got, want)
+    ctx.close()

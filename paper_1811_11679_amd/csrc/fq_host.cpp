@@ -264,12 +264,11 @@ bool same_system(const fq_system &a, const fq_system &b)
     return std::memcmp(a.h1, b.h1, 8 * n2) == 0 && std::memcmp(a.eri, b.eri, 8 * n2 * n2) == 0;
 }
 
-// spans of 256 attempts the attempt partition can hold
-int64_t span_capacity(int64_t mcap, int64_t scap, int W)
-{
-    (void)W;
-    return tiles_of(std::max(mcap * 16, scap * 4), SPAN_MIN);
-}
+// Spans of the attempt partition, one per spawn tile of the shape a context has.
+// A context whose shape follows the list size may run with tiles of half that
+// size, so the array holds twice as many: the attempts an iteration may have
+// depend on the capacities and on the shape the caller chose, not on the plan.
+int64_t span_capacity(int64_t mcap, int64_t scap) { return tiles_of(std::max(mcap * 16, scap * 4), SPAN_MIN); }
 
 Layout make_layout(int R, int W, int64_t mcap, int64_t scap, int64_t tables, int D, int nk, int64_t singles)
 {
@@ -288,7 +287,7 @@ Layout make_layout(int R, int W, int64_t mcap, int64_t scap, int64_t tables, int
     L.sys = take(sizeof(DevSys) * R);
     L.tables = take((size_t)tables);
     L.att = take(8 * (size_t)(mcap + 1));
-    L.span = take(8 * (size_t)(span_capacity(mcap, scap, W) + 2));
+    L.span = take(8 * (size_t)(2 * span_capacity(mcap, scap) + 2));
     L.mpart = take(8 * (size_t)(tiles_of(mcap + scap, MERGE_TILE_MIN) + 2));
     L.mtile = take(8 * (size_t)tiles_of(mcap + scap, MERGE_TILE_MIN));
     L.mrun = take(16 * (size_t)PART_MAX_BLOCKS);
@@ -577,6 +576,8 @@ Grids sized_grids(const fq_ctx *c, double room)
 
 void choose_plan(fq_ctx *c)
 {
+    c->w.att_cap = (span_capacity(c->main_cap, c->spawn_cap) - 1) * SP_T *
+                   spawn_items(dm_method(c->method), c->W, c->grids.spawn_i);
     const int64_t n = c->spawn_hint + c->spawn_hint / 2;
     int p = passes_for(n, c->rb);
     if (p < c->w.sort_p) p = std::min(c->w.sort_p, passes_for(4 * n, c->rb));
@@ -1066,7 +1067,6 @@ fq_status init_system(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc, con
     w.ds.key_sorted = (const uint64_t *)(c->ws + c->L.ds[9]);
     w.main_cap = main_capacity;
     w.spawn_cap = spawn_capacity;
-    w.span_cap = span_capacity(main_capacity, spawn_capacity, c->W);
     w.R = c->R;
     w.rb = c->rb;
     w.hmask = c->hmask;

@@ -94,9 +94,10 @@ constexpr int MERGE_TILE_MIN = 256;
 
 // spawn tiles: SP_T threads of SI attempts each (2, 4 or 8 for keys of up to
 // two words, chosen per context; 2 for longer keys, whose children take more
-// registers); the attempt partition is sized for the smallest tile
+// registers; 4 for pairs)
 constexpr int SP_T = 256;
 constexpr int SPAN_MIN = 2 * SP_T;
+inline int spawn_items(bool pair, int W, int shape) { return W > 2 ? 2 : pair ? 4 : shape; }
 constexpr int PART_MAX_BLOCKS = 8192;
 // largest diagonal-table staging of the new-determinant kernel (bytes of LDS)
 constexpr int ND_LDS_MAX = 65536;
@@ -201,7 +202,8 @@ struct Work {
     SpawnList sp;
     UniqList u;
     DetSpace ds;
-    long long main_cap, spawn_cap, span_cap;
+    long long main_cap, spawn_cap;
+    long long att_cap;  // attempts of an iteration the partition takes
     int32_t R, rb, W, hist_len;
     int32_t sort_p;  // radix passes over the top digits of the sort keys (1..SORT_P_MAX)
     int32_t pad_sort;

@@ -49,7 +49,7 @@ __global__ __launch_bounds__(256) void k_spawn_partition(Work w, int span_len)
         for (int i = threadIdx.x; i < w.sort_p * 256; i += blockDim.x) c->hist[7 - (i >> 8)][i & 255] = 0;
         for (int i = threadIdx.x; i < w.R * (int)(sizeof(EstAcc) / 8); i += blockDim.x) ((long long *)w.acc)[i] = 0;
     }
-    if (nspans + 1 > w.span_cap) {
+    if (total > w.att_cap) {
         if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&c->err, ERR_SPAWN_CAP);
         return;
     }
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
     const long long nspans = (total + SPAN - 1) / SPAN;
     const uint32_t t = c->t;
     const bool ss = c->ss_active != 0;
-    if (block_stops(c) || nspans + 1 > w.span_cap) return;
+    if (block_stops(c) || total > w.att_cap) return;
     const int lane = lane_id(), wid = threadIdx.x >> 6;
     // time-step search: the largest |H_ji| / p_gen of this thread's attempts
     // of replica rs_rep
@@ -448,21 +448,11 @@ static void launch_spawn(const Work &w, const Grids &g, hipStream_t s)
         k_spawn<KIND, W, false, false, SI><<<g.spawn, SP_T, 0, s>>>(w);
 }
 
-// attempts per thread: a tile-shape variant for keys of up to two words; the
-// partition and the spawn must agree on it
-template <int KIND, int W>
-static int spawn_items(const Grids &g)
-{
-    constexpr bool VAR = W <= 2 && !is_pair(KIND);
-    const int si = VAR ? g.spawn_i : (W <= 2 ? 4 : 2);
-    return si != 2 && si != 8 ? (W <= 2 ? 4 : 2) : si;
-}
-
 template <int KIND, int W>
 static void launch_spawn_kind(int part, const Work &w, const Grids &g, hipStream_t s)
 {
     constexpr bool VAR = W <= 2 && !is_pair(KIND);
-    const int si = spawn_items<KIND, W>(g);
+    const int si = spawn_items(is_pair(KIND), W, g.spawn_i);  // the partition and the spawn must agree on it
     if (part == 0) {
         k_spawn_partition<<<g.part, 256, 0, s>>>(w, SP_T * si);
         return;

@@ -515,8 +515,7 @@ def run_single(args):
     ds_active = spec["ss"] is not None
     is_cc = q.get("method", 0) == F.CCMC
     cc = (q["ccmc_truncation"], s["n_alpha"] + s["n_beta"], q["fixed_point_bits"]) if is_cc else None
-    # slots of passes the plan does not make hold the time between two events, as "sort_hist" does
-    passes = max(1, sum(ktimes[f"sort_pass{p}"] > 2.0 * ktimes["sort_hist"] for p in range(8)))
+    passes = max(1, sum(ktimes[f"sort_pass{p}"] > 0.0 for p in range(8)))  # those the iterations made
     tot_bytes = {}
     for a, b in zip(prevk, hk):
         for k, v in algorithmic_bytes(a, b, ctx.W, ds_active=ds_active, ccmc=cc, passes=passes).items():

@@ -321,7 +321,8 @@ fq_status fq_stage_times(const fq_ctx *ctx, double *ms7);
  * projection check, merge partition, merge, new-determinant diagonals, CCMC
  * pairs, end. A slot whose work another launch does or the iteration does not
  * need (begin, the histogram, fix-up, repeat and merge-partition slots; sort passes
- * beyond the one to four an iteration makes) holds the empty interval between two events.
+ * beyond the one to four an iteration makes) holds the empty interval between two events;
+ * the sort passes no iteration of the call made hold zero.
  * *n_slots receives the slot count (24) and *n_iterations the number of timed
  * iterations. */
 fq_status fq_kernel_times(const fq_ctx *ctx, double *ms, int32_t cap, int32_t *n_slots,

@@ -245,6 +245,7 @@ struct Grids {
 // kernels of one iteration, in launch order (per-kernel timing slots; the
 // two CCMC slots are empty for the other methods)
 constexpr int N_KERNEL_SLOTS = 24;
+constexpr int SORT_SLOT = 5;  // first of the eight slots of radix passes
 // enqueue one whole iteration on a stream (ev: N_KERNEL_SLOTS + 1 events or nullptr)
 hipError_t enqueue_iteration(const Work &w, int kind, const Grids &g, hipStream_t s, hipEvent_t *ev);
 // CCMC stages: 0 = prefix of |N_i| and composite-cluster spawns (after the

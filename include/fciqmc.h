@@ -368,11 +368,14 @@ fq_status fq_get_launch(const fq_ctx *ctx, int32_t *blocks, int32_t n);
  * radix-sort keys per thread (8, 12 or 16; tiles of 256 threads). [0] and [1]
  * apply to determinant keys of one or two words (longer keys and pair keys
  * use 2 and 2, resp. 4 and 2); [2] to every context. Defaults 4, 4, 12;
- * until a shape is set, small lists use 2 and 1 of [0] and [1]. A value
+ * small lists use 2 of [0] and 1 of [1] until that shape is set. A value
  * <= 0 keeps the current one; any other value outside the list is FQ_EINVAL
  * (nothing changes). Results do not depend on the shapes (tiles only
  * partition the work; every prefix crossing tiles is exact); only speed does.
- * Changing them drops the captured graphs. */
+ * The attempts of one iteration must fit the spans the capacities give: about
+ * max(32 main_capacity, 8 spawn_capacity), half or twice that where [0] is set
+ * to 2 or 8 (FQ_ECAPACITY otherwise). Changing the shapes drops the captured
+ * graphs. */
 fq_status fq_set_tiles(fq_ctx *ctx, const int32_t *tiles, int32_t n);
 fq_status fq_get_tiles(const fq_ctx *ctx, int32_t *tiles, int32_t n);
 

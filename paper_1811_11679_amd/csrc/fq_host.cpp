@@ -365,7 +365,7 @@ struct fq_ctx {
     // sizes the next iteration is expected to have (those of the last one)
     int64_t spawn_hint = 0, main_hint = 0, att_hint = 0;
     Grids plan{};  // launch geometry of the blocks being enqueued (choose_plan)
-    bool tiles_set = false;  // the caller has chosen the tile shapes
+    bool tile_set[3] = {false, false, false};  // tile shapes the caller has chosen: spawn, merge, sort
     std::vector<double> shift;
     std::vector<int> vary;
     std::vector<int64_t> nprev;
@@ -531,8 +531,8 @@ Grids sized_grids(const fq_ctx *c, double room)
         return (int)std::max<int64_t>(1, std::min<int64_t>(cap, n));
     };
     const int64_t ns = c->spawn_hint, nm = c->main_hint + c->spawn_hint;
-    if (!c->tiles_set) {
-        // Tile shapes by size, unless the caller has set them. On a list of
+    {
+        // Tile shapes by size, each unless the caller has set it. On a list of
         // few tiles a thread's serial work is what counts (8-site ring, 4e3
         // determinants: 108 us an iteration with four attempts and positions
         // per thread, 92 with two and one; 14 electrons, 8e5 determinants: 194
@@ -542,9 +542,10 @@ Grids sized_grids(const fq_ctx *c, double room)
         // (A shape in use is kept a little beyond its line.)
         const double few_m = c->plan.merge_i == 1 ? 40 : 32, few_s = c->plan.spawn_i == 2 ? 40 : 32;
         const double rounds = c->plan.spawn_i == 2 ? 2.25 : 2.0;
-        if ((double)nm < few_m * 256 * g.merge_i) g.merge_i = 1;
-        if ((double)c->att_hint < few_s * SP_T * g.spawn_i ||
-            (c->kind == FQ_MOLECULAR && (double)c->att_hint < rounds * SP_T * g.spawn_i * g.spawn))
+        if (!c->tile_set[1] && (double)nm < few_m * 256 * g.merge_i) g.merge_i = 1;
+        if (!c->tile_set[0] &&
+            ((double)c->att_hint < few_s * SP_T * g.spawn_i ||
+             (c->kind == FQ_MOLECULAR && (double)c->att_hint < rounds * SP_T * g.spawn_i * g.spawn)))
             g.spawn_i = 2;
     }
     g.part = fit(c->grids.part, c->att_hint / SPAN_MIN, 256);
@@ -1940,7 +1941,7 @@ fq_status fq_set_tiles(fq_ctx *c, const int32_t *tiles, int32_t n)
     for (int i = 0; i < n && i < 3; ++i)
         if (tiles[i] > 0) {
             *dst[i] = tiles[i];
-            c->tiles_set = true;
+            c->tile_set[i] = true;
         }
     drop_graphs(c);
     return FQ_OK;

@@ -359,9 +359,10 @@ __global__ __launch_bounds__(256) void k_det_project_fp64(Work w, int mode)
         // y = sum_j K_ij n_j, exact in fixed point (2^-64), rounded once: the
         // order of the terms over lanes and the wave reduction does not matter.
         // A term x, truncated at 2^-64, is h 2^-20 + l 2^-64 with whole numbers
-        // h = trunc(x 2^20) and l: their FP64 sums are exact below 2^53, so lanes
-        // of up to 512 terms below 2^28 add them in FP64; beyond that the wave
-        // takes the limbs. 8 x 2000 rows of 2000: 87 us by limbs alone, 48 now.
+        // h = trunc(x 2^20) and l: their FP64 sums are exact up to 2^53, so a lane
+        // of k <= 512 terms below 2^33 / k (2^28 for the 32 terms of a row of
+        // 2000) adds them in FP64; beyond that the wave takes the limbs. 8 x 2000
+        // rows of 2000: 87 us by limbs alone, 48 now.
         long long a0 = 0, a1 = 0, a2 = 0, a3 = 0;
         double pabs = 0.0, sh = 0.0, sl = 0.0, big = 0.0;
         bool odd = false;  // a NaN: the limbs decide

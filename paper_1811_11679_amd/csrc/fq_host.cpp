@@ -362,8 +362,17 @@ struct fq_ctx {
     int cur = 0;
     int64_t main_cap = 0, spawn_cap = 0;
     Grids grids{};
-    // sizes the next iteration is expected to have (those of the last one)
+    // sizes the next iterations are expected to have
     int64_t spawn_hint = 0, main_hint = 0, att_hint = 0;
+    // records and determinants of the last iterations of this list, oldest first
+    // (none after a list has been put in place)
+    struct Sizes {
+        double spawn, main;
+    };
+    std::vector<Sizes> recent;
+    // growth the hints allow for, and that of the plan in use
+    double room = 1.0, plan_room = 1.0;
+    double repeat = 1.0;  // records per determinant of the last iteration
     Grids plan{};  // launch geometry of the blocks being enqueued (choose_plan)
     bool tile_set[3] = {false, false, false};  // tile shapes the caller has chosen: spawn, merge, sort
     std::vector<double> shift;
@@ -504,21 +513,27 @@ void drop_graphs(fq_ctx *c)
     }
 }
 
-// Radix passes for n spawned records: enough top digits that a group of equal
-// digits holds at most 32 records on average, which the collapse ranks by
-// counting (measured: a pass costs 8..15 us on a small list and 90 us at 7e6
-// records; without the third pass the collapse of 6e6 records took 545 us).
-// The replica id takes rb of the digits' bits and one replica may hold nearly
-// all records, so those bits do not count.
-int passes_for(int64_t n, int rb)
+// Radix passes for n spawned records, with half as many again to spare: enough
+// top digits that a group of equal digits holds at most 32 records on average,
+// which the collapse ranks by counting (measured: a pass costs 8..15 us on a small
+// list and 90 us at 7e6 records; without the third pass the collapse of 6e6
+// records took 545 us). The replica id takes rb of the digits' bits and one
+// replica may hold nearly all records, so those bits do not count.
+// repeat: records per determinant. Where a few determinants hold most records
+// their groups are large long before the average is, so one pass is left earlier
+// (iterations with one pass and with two: 4.7e3 records once each 106 and 113 us,
+// 3.6e3 at 1.9 each 78 and 84, 5.4e3 at 2.3 each 92 and 92, 2.5e3 at 5 each 112
+// and 99, 5.0e3 at 8 each 129 and 109).
+int passes_for(int64_t n, double repeat, int rb)
 {
     int p = 1;
-    while (p < SORT_P_MAX && (8 * p <= rb || n > (int64_t(32) << (8 * p - rb)))) ++p;
+    while (p < SORT_P_MAX && (8 * p <= rb || n + n / 2 > (int64_t(32) << (8 * p - rb)))) ++p;
+    if (p == 1 && (double)n * repeat > (double)(int64_t(32) << (8 - rb))) p = 2;
     return p;
 }
 
 // The plan of the next block of iterations: radix passes and launch geometry
-// for the sizes the last block ended with. Any plan gives the same lists (the
+// for the sizes it is expected to end with. Any plan gives the same lists (the
 // kernels take their tiles by ticket or stride and read their sizes on the
 // device); blocks without a tile only cost their start: at 4e3 determinants
 // the kernels of an iteration took 165 us at the full grids. A plan is kept
@@ -575,17 +590,59 @@ Grids sized_grids(const fq_ctx *c, double room)
     return g;
 }
 
+// How many of the next n iterations to plan as one block. A plan made for a
+// fraction of the records a block ends with costs far more than it saves: with
+// one pass the reduction finds all of them in 256 groups (the 14-electron gas in
+// 123 plane waves grown from 2e3 walkers to 2.7e6 records in ten iterations: 178 ms
+// planned as one block, 3.5 ms now). So a block ends before the sizes have grown
+// by GROWTH_ROOM at the rate of the last ten iterations, and the plan is for the
+// sizes it will end with. A list just put in place has no rate: its first
+// iteration is planned for a record per attempt, the next two for eight times that
+// one's sizes.
+constexpr double GROWTH_ROOM = 16.0, GROWTH_FIRST = 8.0, GROWTH_ENDED = 1.5;
+// lists so small that any plan serves them count as this size
+constexpr double GROWTH_FLOOR = 512.0;
+int expect_sizes(fq_ctx *c, int n)
+{
+    const size_t m = c->recent.size();
+    if (m == 0) {  // (upload_main has set the sizes)
+        c->room = GROWTH_FIRST;
+        return 1;
+    }
+    double spawn = GROWTH_FIRST, main = GROWTH_FIRST;
+    if (m == 1) {
+        n = std::min(n, 2);
+    } else {
+        const size_t k = std::min<size_t>(m - 1, 10);
+        const auto &a = c->recent[m - 1 - k], &b = c->recent[m - 1];
+        auto rate = [&](double then, double now) { return std::log(std::max(1.0, now / std::max(then, GROWTH_FLOOR))) / (double)k; };
+        const double rs = rate(a.spawn, b.spawn), rm = rate(a.main, b.main), most = std::max(rs, rm);
+        if (most * n > std::log(GROWTH_ROOM)) n = std::max(1, (int)(std::log(GROWTH_ROOM) / most));
+        spawn = std::exp(rs * n);
+        main = std::exp(rm * n);
+    }
+    auto grown = [](int64_t x, double by, int64_t cap) { return (int64_t)std::min((double)x * by, (double)std::max(x, cap)); };
+    c->spawn_hint = grown(c->spawn_hint, spawn, c->spawn_cap);
+    c->main_hint = grown(c->main_hint, main, c->main_cap);
+    c->att_hint = grown(c->att_hint, spawn, INT64_MAX / 4);
+    c->room = std::max(spawn, main);
+    return n;
+}
+
 void choose_plan(fq_ctx *c)
 {
     c->w.att_cap = (span_capacity(c->main_cap, c->spawn_cap) - 1) * SP_T *
                    spawn_items(dm_method(c->method), c->W, c->grids.spawn_i);
-    const int64_t n = c->spawn_hint + c->spawn_hint / 2;
-    int p = passes_for(n, c->rb);
-    if (p < c->w.sort_p) p = std::min(c->w.sort_p, passes_for(4 * n, c->rb));
+    const int64_t n = c->spawn_hint;
+    int p = passes_for(n, c->repeat, c->rb);
+    // what was planned for growth that has ended is planned anew
+    const bool ended = c->plan_room > GROWTH_ENDED && c->room <= GROWTH_ENDED;
+    // (passes in use are kept a little below their line)
+    if (!ended && p < c->w.sort_p) p = std::min(c->w.sort_p, passes_for(n + n / 4, c->repeat, c->rb));
     const Grids lo = sized_grids(c, 1.0), hi = sized_grids(c, 8.0);
     auto within = [](int x, int a, int b) { return x >= a && x <= b; };
     const Grids &g = c->plan;
-    const bool keep = p == c->w.sort_p && g.ss == lo.ss && within(g.part, lo.part, hi.part) &&
+    const bool keep = !ended && p == c->w.sort_p && g.ss == lo.ss && within(g.part, lo.part, hi.part) &&
                       within(g.spawn, lo.spawn, hi.spawn) && within(g.sort, lo.sort, hi.sort) &&
                       within(g.reduce, lo.reduce, hi.reduce) && within(g.merge, lo.merge, hi.merge) &&
                       within(g.newdiag, lo.newdiag, hi.newdiag) && within(g.ccmc, lo.ccmc, hi.ccmc) && g.spawn_i == lo.spawn_i &&
@@ -593,6 +650,7 @@ void choose_plan(fq_ctx *c)
     if (keep) return;
     c->w.sort_p = p;
     c->plan = sized_grids(c, 2.0);
+    c->plan_room = c->room;
     drop_graphs(c);
 }
 
@@ -678,7 +736,10 @@ fq_status upload_main(fq_ctx *c, const std::vector<HostEntry> &e)
     HIPCHK(c, hipStreamSynchronize(c->stream));
     c->main_hint = n;
     c->att_hint = ctl.n_att_new;
-    c->spawn_hint = std::min<int64_t>(ctl.n_att_new / 4, c->spawn_cap);  // a fraction of the attempts spawns
+    // at most a record per attempt, and as many by the clusters
+    c->spawn_hint = std::min<int64_t>((c->method == FQ_CCMC ? 2 : 1) * ctl.n_att_new, c->spawn_cap);
+    c->recent.clear();
+    c->repeat = 1.0;
     return FQ_OK;
 }
 
@@ -1362,10 +1423,11 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
     constexpr int NE = N_KERNEL_SLOTS + 1;
     std::vector<hipEvent_t> evs;
     int done = 0;
+    int64_t whole = c->t;  // end of the iterations up to the next decision point
     while (done < n_iterations) {
-        // CCMC: the prefix of |N_i| travels in look-back words of 38 bits; a
-        // block of iterations starts only with room for its growth
-        if (c->method == FQ_CCMC && c->last[0].n_walkers_units >= (int64_t(1) << 36))
+        // CCMC: the prefix of |N_i| travels in look-back words of 38 bits; the
+        // iterations up to a decision point start only with room for their growth
+        if (c->t >= whole && c->method == FQ_CCMC && c->last[0].n_walkers_units >= (int64_t(1) << 36))
             return fail(c, FQ_EOVERFLOW, "CCMC: the excip population exceeds 2^36 units");
         // iterations until the next host decision point (shift update, D selection, end)
         int64_t stop = c->t + (n_iterations - done);
@@ -1384,6 +1446,8 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
             if (c->L.single_key > c->L.st_ccmc)
                 HIPCHK(c, fill0(c->stream, c->ws + c->L.st_ccmc, c->L.single_key - c->L.st_ccmc));
         }
+        whole = stop;
+        stop = c->t + expect_sizes(c, (int)(stop - c->t));
         choose_plan(c);
         const int64_t t0 = c->t;
         const int cur0 = c->cur;
@@ -1512,9 +1576,14 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
         c->att_hint = ctl.n_att_new;
         fold_spawn_ratio(c, t0 + 1, stop);
         for (int64_t it = t0 + 1; it <= stop; ++it) {
+            c->recent.push_back({0.0, 0.0});
+            double distinct = 0.0;
             for (int r = 0; r < c->R; ++r) {
                 fq_estimators_t e;
                 estimators_from_acc(c, r, c->h_hist[(size_t)(it % HIST_LEN) * c->R + r], e);
+                c->recent.back().spawn += (double)e.n_spawned;
+                c->recent.back().main += (double)e.n_occupied;
+                distinct += (double)e.n_spawn_events;
                 if (it % A == 0) {
                     const double target = c->qmc[r].target_population * std::ldexp(1.0, c->qmc[r].fixed_point_bits);
                     const int64_t nw = e.n_walkers_units;
@@ -1560,7 +1629,9 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
                 c->hist[r].push_back(e);
                 c->last[r] = e;
             }
+            c->repeat = c->recent.back().spawn / std::max(1.0, distinct);
         }
+        if (c->recent.size() > 32) c->recent.erase(c->recent.begin(), c->recent.end() - 16);
         c->t = stop;
         done += nb;
         for (int r = 0; r < c->R; ++r) c->h_shift[r] = c->shift[r];

@@ -92,6 +92,9 @@ __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
     const uint32_t t = c->t;
     const bool ss = c->ss_active != 0;
     if (block_stops(c) || total > w.att_cap) return;
+    // a plan has up to twice the blocks its tiles need: the others stage no tables
+    // (2 electrons in 30 orbitals, 2e5 walkers: 124 us an iteration with, 103 without)
+    if (blockIdx.x >= nspans) return;
     const int lane = lane_id(), wid = threadIdx.x >> 6;
     // time-step search: the largest |H_ji| / p_gen of this thread's attempts
     // of replica rs_rep

@@ -42,31 +42,31 @@ def test_long_keys_on_truncated_sort_keys(ecut, electrons, bits, walkers, tau):
     ctx.close()
 
 
-# One pass orders 256 groups; the list grows from a handful of records within the
-# block that was planned for it: groups of 128 to 1024 mixed records go through the
-# network, larger ones are picked apart. With 20 hash bits, in two instances,
-# determinants share sort keys in both.
-@pytest.mark.parametrize("ecut,tau,walkers", [(5, 0.02, 2e3), (5, 0.02, 2e4), (9, 0.02, 2e2), (9, 0.02, 2e3),
-                                              (14, 0.01, 3e2), (14, 0.01, 2e3)])
-@pytest.mark.parametrize("bits", [64, 20])
+# One pass orders 256 groups. The second and third iteration are planned together for
+# eight times the records of the first; with these time steps the list grows far more:
+# groups of 128 to 1024 mixed records go through the network, larger ones are picked
+# apart. With 20 hash bits, in two instances, determinants share sort keys in both.
+@pytest.mark.parametrize("ecut,tau,walkers,bits", [
+    (5, 0.4, 1200, 64), (5, 1.5, 1200, 64), (9, 0.2, 600, 64), (9, 0.6, 600, 64), (14, 0.1, 400, 64), (14, 0.4, 400, 64),
+    (5, 0.6, 300, 20), (5, 3.0, 300, 20), (9, 0.3, 200, 20), (9, 0.9, 200, 20), (14, 0.15, 200, 20), (14, 0.6, 200, 20)])
 def test_growth_beyond_the_plan(ecut, tau, walkers, bits):
     n = 1 if bits == 64 else 2
-    if n > 1:
-        walkers = min(walkers, 4e3)
     sysd = dict(kind="ueg", rs=1.0, ecut_n2=ecut, n_alpha=7, n_beta=7)
-    q = dict(workloads.UEG14["qmc"], tau=tau, init_pop=walkers, target_population=1e12, initiator=0)
-    ctx = gpu_context([sysd] * n, [q] * n, replicas=list(range(n)), main_capacity=1 << 23, spawn_capacity=1 << 22)
+    q = dict(workloads.UEG14["qmc"], tau=tau, init_pop=walkers, target_population=1e15, initiator=0)
+    ctx = gpu_context([sysd] * n, [q] * n, replicas=list(range(n)), main_capacity=1 << 23, spawn_capacity=1 << 23)
     if bits < 64:
         ctx.set_sort_key_bits(bits)
-    ctx.step(9)
+    ctx.set_timing(True)
+    ctx.step(3)
+    times, _ = ctx.kernel_times()
+    assert times["sort_pass0"] > 0.0 and times["sort_pass1"] == 0.0
     for r in range(n):
         run = O.Run(oracle_system(sysd), oracle_qmc(sysd, q, replica=r))
-        run.step(9)
-        where = f"cutoff {ecut}, {walkers:g} walkers, {bits} bits, instance {r}"
+        run.step(3)
+        where = f"cutoff {ecut}, time step {tau:g}, {bits} bits, instance {r}"
         assert_same_lists(ctx, run, instance=r, where=where)
-        for got in ctx.history(r)[-1:]:
-            assert_same_estimators(got, run.estimators(), where=where)
-    records = ctx.estimators(0)["n_spawned"]
-    say(f"[case] {ctx.W} words, {bits} bits: {records * n} records in 256 groups")
-    assert records * n / 256 > 128
+        assert_same_estimators(ctx.history(r)[-1], run.estimators(), where=where)
+    records = sum(ctx.estimators(r)["n_spawned"] for r in range(n))
+    say(f"[case] {ctx.W} words, {bits} bits: {records} records in 256 groups")
+    assert records / 256 > 128
     ctx.close()

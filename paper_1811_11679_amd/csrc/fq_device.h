@@ -611,7 +611,18 @@ __device__ bool gen_ueg(const UegTables &s, const uint64_t (&D)[W], uint32_t w0,
 // summed a second time. Bound: vector ALU, about 3000 instructions an attempt
 // with the rest of the spawn. Spawn of 16 electrons in 30 orbitals: 348 -> 215 us
 // at 1.05e6 determinants, eight instances 542 -> 335 us.
+//
+// A spawn kernel of its own (its registers slowed the loops of 17 electrons by a
+// seventh when they shared one), taken from 8 electrons, or from 10 beside a table
+// so large that it leaves few blocks to a compute unit, to 16, the rows that fit
+// the registers. Spawn of 3e7 attempts with the loops and with the sums, us:
+//   electrons         2     6     8    10    12    16
+//   30 orbitals     913  1565  2000  2524  3136  4658
+//     sums         1290  1759  1895  2068  2200  2472
+//   44 orbitals    1234  2013  2531  3128  3867  5639
+//     sums         1914  2594  2836  3075  3310  3725
 constexpr int HB_ROWS = 16;
+inline int hb_rows_min(int table_bytes) { return table_bytes <= 16384 ? 8 : 10; }
 struct PairSums {
     double row[HB_ROWS];  // running sum before row i (one row per electron)
     double T;
@@ -683,7 +694,7 @@ struct PairSums {
 // Heat-bath doubles (weights |<AB||PQ>| tabulated per pair) with uniform
 // singles taken with probability p_single. The double branch uses a second
 // Philox block, drawn only when needed.
-template <int W>
+template <int W, bool SUMS = false>
 __device__ bool gen_heatbath(const DevSys &s, double p_single, const uint64_t (&D)[W], const U4 &r0,
                              uint32_t attempt, uint32_t t, uint64_t hsh, uint32_t k0, uint32_t k1,
                              uint64_t (&child)[W], double &pgen, double &h, const double *stri = nullptr)
@@ -725,7 +736,7 @@ __device__ bool gen_heatbath(const DevSys &s, double p_single, const uint64_t (&
     int held = 0;  // (an imported determinant may hold another number of electrons)
 #pragma unroll
     for (int i = 0; i < W; ++i) held += __popcll(D[i]);
-    if (stri && N <= HB_ROWS && held == N) {
+    if (SUMS && held == N) {
         PairSums sums;
         sums.total<W>(stri, nso, N, D);
         T = sums.T;

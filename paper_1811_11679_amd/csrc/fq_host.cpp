@@ -1291,6 +1291,7 @@ fq_status init_system(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc, con
         if (bytes <= 32768) {
             c->grids.spawn_lds = (int)bytes;
             w.lds_tables = (int32_t)bytes;
+            c->grids.pair_sums = c->sys[0].nel >= hb_rows_min((int)bytes) && c->sys[0].nel <= HB_ROWS;
         }
     }
     // UEG generator tables staged in LDS by the single-replica spawn kernel

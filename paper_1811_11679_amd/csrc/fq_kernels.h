@@ -231,6 +231,7 @@ struct Work {
 struct Grids {
     int scan, part, spawn, sort, reduce, merge, move, det;
     int spawn_lds;  // dynamic LDS bytes of the spawn kernel
+    int pair_sums = 0;  // the heat-bath spawn sums pair weights from registers
     int newdiag;    // blocks of the new-determinant diagonal kernel
     // tile shapes (compile-time variants chosen at run time; results do not
     // depend on them): spawning attempts per thread (2, 4, 8; keys of up to two

@@ -67,12 +67,14 @@ __global__ __launch_bounds__(256) void k_spawn_partition(Work w, int span_len)
 // parameters are uniform over the grid and a determinant's hash is its sort key.
 // LT (single-replica electron gas): the generator's small tables are staged in
 // LDS; a compile-time choice, so that their loads are LDS loads.
+// SUMS (heat-bath, with LT): the pair weights of a determinant are summed from
+// registers (PairSums).
 //
 // LDS per block: the attempt offsets of the tile's parents and the first
 // SP_STAGE spawn records (written out coalesced); records beyond that, rare at
 // the spawn rates of the method, go to global memory directly.
 constexpr int SP_STAGE = 256;
-template <int KIND, int W, bool MULTI, bool LT, int SP_I>
+template <int KIND, int W, bool MULTI, bool LT, int SP_I, bool SUMS = false>
 __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
 {
     Ctl *c = w.ctl;
@@ -264,8 +266,8 @@ __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
                 else if constexpr (BK == K_UEG)
                     ok = gen_ueg<WG>(LT ? lu : sy.u, gdet, r0.x, r0.y, gchild, pgen, hv);
                 else
-                    ok = gen_heatbath<WG>(sy, rp.p_single, gdet, r0, (uint32_t)k, t, h, rp.k0, rp.k1, gchild, pgen, hv,
-                                          hb_tri);
+                    ok = gen_heatbath<WG, SUMS>(sy, rp.p_single, gdet, r0, (uint32_t)k, t, h, rp.k0, rp.k1, gchild, pgen,
+                                                hv, hb_tri);
 #pragma unroll
                 for (int q = 0; q < W; ++q) child[it][q] = key[q];
 #pragma unroll
@@ -440,8 +442,12 @@ __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
 template <int KIND, int W, int SI>
 static void launch_spawn(const Work &w, const Grids &g, hipStream_t s)
 {
-    constexpr bool TAB = KIND == K_UEG || KIND == K_MOLECULAR;
-    if (w.R > 1 && TAB && w.lds_tables > 0)
+    constexpr bool TAB = KIND == K_UEG || KIND == K_MOLECULAR, PAIRS = KIND == K_MOLECULAR;
+    if (PAIRS && g.pair_sums && w.R > 1)
+        k_spawn<KIND, W, true, TAB, SI, PAIRS><<<g.spawn, SP_T, g.spawn_lds, s>>>(w);
+    else if (PAIRS && g.pair_sums)
+        k_spawn<KIND, W, false, TAB, SI, PAIRS><<<g.spawn, SP_T, g.spawn_lds, s>>>(w);
+    else if (w.R > 1 && TAB && w.lds_tables > 0)
         k_spawn<KIND, W, true, TAB, SI><<<g.spawn, SP_T, g.spawn_lds, s>>>(w);
     else if (w.R > 1)
         k_spawn<KIND, W, true, false, SI><<<g.spawn, SP_T, 0, s>>>(w);

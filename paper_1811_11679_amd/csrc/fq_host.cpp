@@ -1457,7 +1457,8 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
             evs.resize((size_t)nb * NE);
             for (auto &e : evs) (void)hipEventCreate(&e);
         }
-        const bool use_graph = c->graph && !c->timing && nb == A;
+        // (a plan for a growing list does not last long enough to be captured)
+        const bool use_graph = c->graph && !c->timing && nb == A && c->room <= GROWTH_ENDED;
         if (use_graph) {
             // one captured block of A iterations per main-list parity, replayed
             const int b = c->cur;

@@ -27,6 +27,8 @@
 #include "fq_kernels.h"
 #include "fq_scan.h"
 
+#include <type_traits>
+
 namespace fq {
 
 constexpr int CL_T = 256, CL_I = 4;
@@ -114,9 +116,69 @@ __device__ long long group_end(const uint64_t *skey, long long lo, long long hi,
     return lo;
 }
 
+// f(place, sort key) for a thread's share of the places [lo, hi), U keys in flight
+template <int U, typename F>
+__device__ __forceinline__ void scan_keys(const uint64_t *skey, long long lo, long long hi, F &&f)
+{
+    for (long long e = lo + threadIdx.x; e < hi; e += U * CL_T) {
+        uint64_t x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = skey[U == 1 ? e : min(e + u * CL_T, hi - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (U == 1 || e + u * CL_T < hi) f(e + u * CL_T, x[u]);
+    }
+}
+
+// Sum and count (initiators above bit 32) of this thread's records of sort key k and
+// the determinant det, U in flight; true if it met another determinant on that key.
+template <int W, int U>
+__device__ __forceinline__ bool group_sum(const uint64_t *rec, const uint64_t *skey, const uint32_t *idx, long long lo,
+                                          long long hi, uint64_t k, const uint64_t (&det)[W], long long &sum, long long &cnt)
+{
+    sum = cnt = 0;
+    bool mixed = false;
+    for (long long e = lo + threadIdx.x; e < hi; e += U * CL_T) {
+        uint64_t x[U], r[U][W + 1];
+        uint32_t j[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const long long at = U == 1 ? e : min(e + u * CL_T, hi - 1);
+            x[u] = skey[at];
+            j[u] = idx[at];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (U == 1 && x[u] != k) continue;
+#pragma unroll
+            for (int q = 0; q <= W; ++q) r[u][q] = rec[(size_t)j[u] * (W + 1) + q];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (e + u * CL_T >= hi || x[u] != k) continue;
+            bool here = true;
+#pragma unroll
+            for (int q = 0; q < W; ++q) here = here && r[u][q] == det[q];
+            if (!here) {
+                mixed = true;
+                continue;
+            }
+            sum += (int32_t)(uint32_t)r[u][W];
+            cnt += 1ll + ((uint32_t)(r[u][W] >> 32) ? 1ll << 32 : 0ll);
+        }
+    }
+    return mixed;
+}
+
 // skey, idx: the list as the passes left it; spare: the other index buffer,
 // free here (places of an oversized tile's selected records)
-template <int W>
+// HEAVY, for lists with many records per determinant (the host's rule): a block
+// keeps several keys and records of an oversized group in flight. All records of a
+// determinant fall to one block, so their latency is what such a list waits for
+// (3.6e6 records on 12 determinants: 1530 -> 950 us, 3.2e7 on 4900: 2700 -> 1710);
+// in the other kernel the registers for it would spill those of the windows' path,
+// which made every case 2 to 9% slower.
+template <int W, bool HEAVY>
 __global__ __launch_bounds__(CL_T, 4) void k_collapse(Work w, const uint64_t *skey, const uint32_t *idx, uint32_t *spare,
                                                    int passes)
 {
@@ -125,6 +187,7 @@ __global__ __launch_bounds__(CL_T, 4) void k_collapse(Work w, const uint64_t *sk
     long long *tab = (long long *)dyn_lds;  // estimator table, acc_rows(R) rows
     const int rl = acc_rows(w.R);
     acc_table_clear(tab, rl);
+    constexpr int UK = HEAVY ? 8 : 1, UR = !HEAVY ? 1 : W <= 2 ? 8 : W == 4 ? 4 : 2;
     constexpr bool STAGE = W <= 2;          // the window's keys in LDS; longer ones are gathered again for the output
     __shared__ uint64_t s_x[CL_CAP + 1];    // sort keys of the window, then prefix sums at the heads
     __shared__ uint64_t s_key[STAGE ? W : 1][STAGE ? CL_CAP : 1];
@@ -137,6 +200,7 @@ __global__ __launch_bounds__(CL_T, 4) void k_collapse(Work w, const uint64_t *sk
     __shared__ int s_first, s_end, s_coll, s_cnt, s_swap, s_big;
     __shared__ uint64_t s_lastk[W + 1];     // the tile's last determinant: key, then sort key
     __shared__ long long s_red[16];
+    __shared__ int s_bits[65];              // records of a group by their highest difference from its lowest key
     const long long n = (long long)min(c->n_spawn, (unsigned long long)w.spawn_cap);
     const long long ntiles = (n + CL_SPAN - 1) / CL_SPAN;
     const int sh = 64 - 8 * passes;
@@ -202,12 +266,16 @@ __global__ __launch_bounds__(CL_T, 4) void k_collapse(Work w, const uint64_t *sk
         }
         // An oversized tile goes through its records in windows: whole groups
         // while they fit; a group that does not fit and holds one sort key is
-        // summed as it is; any other is cut into ranges [wl, wl | mask(lev)] of
-        // sort keys whose records are picked out of it.
+        // summed as it is; any other is cut into ranges [wl, wu] of sort keys whose
+        // records are picked out of it: from the lowest key left to the last that
+        // agrees with it above the highest bit with which they fit a window, or
+        // that key alone, summed as it is, if its own records do not. (Three trips
+        // over the group a range. Ranges found by halving took some 200 trips for
+        // two keys: the seven-site ring at 1e6 records on 1225 determinants, 11
+        // pairs of which share a group, 1280 us an iteration, 344 now.)
         long long written = 0, gc = g0, ge = g1;
         bool sub = false;
-        uint64_t wl = 0, wend = 0;
-        int lev = 0;
+        uint64_t wl = 0, wu = 0, wend = 0;
         for (;;) {
             int m = (int)(g1 - g0);
             bool hot = false, picked = false;
@@ -238,7 +306,7 @@ __global__ __launch_bounds__(CL_T, 4) void k_collapse(Work w, const uint64_t *sk
                         ge = group_end(skey, gc, g1, p, sh);
                         wl = skey[gc];
                         bool same = true;
-                        for (long long e = gc + tid; e < ge; e += CL_T) same = same && skey[e] == wl;
+                        scan_keys<UK>(skey, gc, ge, [&](long long, uint64_t x) { same = same && x == wl; });
                         __syncthreads();
                         if (tid == 0) s_cnt = 0;
                         __syncthreads();
@@ -248,37 +316,63 @@ __global__ __launch_bounds__(CL_T, 4) void k_collapse(Work w, const uint64_t *sk
                         if (s_cnt) {
                             wl = p << sh;
                             wend = wl | ((1ull << sh) - 1);
-                            lev = sh - 4;
                             continue;
                         }
                         hot = true;
-                        wend = wl;
-                        lev = 0;
+                        wu = wend = wl;
                     }
                 } else {
-                    for (;;) {
-                        while (lev > 0 && (wl & ((1ull << lev) - 1))) --lev;
-                        const uint64_t wu = wl | ((1ull << lev) - 1);
-                        __syncthreads();
-                        if (tid == 0) s_cnt = 0;
-                        __syncthreads();
-                        int mine = 0;
-                        for (long long e = gc + tid; e < ge; e += CL_T) mine += skey[e] >= wl && skey[e] <= wu;
-                        if (mine) atomicAdd(&s_cnt, mine);
-                        __syncthreads();
-                        m = s_cnt;
-                        hot = m > CL_CAP && lev == 0;
-                        if (m <= CL_CAP || hot) break;
-                        lev = lev > 4 ? lev - 4 : 0;
+                    // the group's next sort key at or above wl, and its records
+                    // by the highest bit in which they differ from that key
+                    uint64_t next = ~0ull;
+                    bool any = false;
+                    scan_keys<UK>(skey, gc, ge, [&](long long, uint64_t x) {
+                        any = any || x >= wl;
+                        if (x >= wl && x < next) next = x;
+                    });
+#pragma unroll
+                    for (int o = 32; o > 0; o >>= 1) {
+                        const uint64_t x = (uint64_t)__shfl_xor((unsigned long long)next, o, 64);
+                        next = x < next ? x : next;
                     }
-                    if (m > 0 && !hot) {
-                        const uint64_t wu = wl | ((1ull << lev) - 1);
+                    __syncthreads();
+                    if (tid == 0) s_cnt = 0;
+                    if (tid <= 64) s_bits[tid] = 0;
+                    if (lane_id() == 0) s_red[tid >> 6] = (long long)next;
+                    __syncthreads();
+                    if (any) s_cnt = 1;
+                    __syncthreads();
+                    if (s_cnt == 0) {
+                        sub = false;
+                        gc = ge;
+                        continue;
+                    }
+                    wl = (uint64_t)s_red[0];
+                    for (int q = 1; q < CL_T / 64; ++q) wl = min(wl, (uint64_t)s_red[q]);
+                    int equal = 0;
+                    scan_keys<UK>(skey, gc, ge, [&](long long, uint64_t x) {
+                        if (x == wl)
+                            ++equal;
+                        else if (x > wl)
+                            atomicAdd(&s_bits[64 - __clzll((long long)(x ^ wl))], 1);
+                    });
+                    if (equal) atomicAdd(&s_bits[0], equal);
+                    __syncthreads();
+                    m = s_bits[0];
+                    hot = m > CL_CAP;
+                    wu = wl;
+                    for (int b = 1; b <= sh && !hot && m + s_bits[b] <= CL_CAP; ++b) {
+                        m += s_bits[b];
+                        wu = wl | ((1ull << b) - 1);
+                    }
+                    if (!hot) {
                         picked = true;
                         __syncthreads();
                         if (tid == 0) s_cnt = 0;
                         __syncthreads();
-                        for (long long e = gc + tid; e < ge; e += CL_T)
-                            if (skey[e] >= wl && skey[e] <= wu) spare[gc + atomicAdd(&s_cnt, 1)] = (uint32_t)(e - gc);
+                        scan_keys<UK>(skey, gc, ge, [&](long long e, uint64_t x) {
+                            if (x >= wl && x <= wu) spare[gc + atomicAdd(&s_cnt, 1)] = (uint32_t)(e - gc);
+                        });
                         __syncthreads();
 #pragma unroll
                         for (int r = 0; r < CL_I; ++r) {
@@ -315,19 +409,8 @@ __global__ __launch_bounds__(CL_T, 4) void k_collapse(Work w, const uint64_t *sk
                 bool mixed = false;
                 bool one = true;  // the first round: the key just read
                 for (int d = 0;; ++d) {
-                    long long sum = 0, cnt = 0;
-                    for (long long e = gc + tid; e < ge; e += CL_T) {
-                        if (skey[e] != wl) continue;
-                        uint64_t k[W];
-                        rec_key<W>(w, idx[e], k);
-                        if (!key_eq<W>(k, prev)) {
-                            mixed = true;
-                            continue;
-                        }
-                        const uint64_t ai = w.sp.rec[(size_t)idx[e] * (W + 1) + W];
-                        sum += (int32_t)(uint32_t)ai;
-                        cnt += 1ll + ((uint32_t)(ai >> 32) ? 1ll << 32 : 0ll);
-                    }
+                    long long sum, cnt;
+                    if (group_sum<W, UR>(w.sp.rec, skey, idx, gc, ge, wl, prev, sum, cnt)) mixed = true;
                     long long es, ec, ts, tc;
                     block_excl_scan2(sum, cnt, es, ec, ts, tc, s_red);
                     if (one) {
@@ -661,13 +744,11 @@ __global__ __launch_bounds__(CL_T, 4) void k_collapse(Work w, const uint64_t *sk
             }
             if (!over) break;
             if (sub) {
-                const uint64_t wu = wl | ((1ull << lev) - 1);
                 if (wu >= wend) {
                     sub = false;
                     gc = ge;
                 } else {
                     wl = wu + 1;
-                    lev = min(lev + 4, sh - 4);
                 }
             }
         }
@@ -691,11 +772,18 @@ hipError_t enqueue_collapse(const Work &w, const Grids &g, int passes, hipStream
     const uint32_t *ix = passes & 1 ? w.sp.idx2 : w.sp.idx;
     uint32_t *spare = passes & 1 ? w.sp.idx : w.sp.idx2;
     const int accb = acc_rows(w.R) * EST_FIELDS * 8;
+    auto launch = [&](auto width) {
+        constexpr int W = decltype(width)::value;
+        if (g.heavy)
+            k_collapse<W, true><<<g.reduce, CL_T, accb, s>>>(w, sk, ix, spare, passes);
+        else
+            k_collapse<W, false><<<g.reduce, CL_T, accb, s>>>(w, sk, ix, spare, passes);
+    };
     switch (w.W) {
-    case 1: k_collapse<1><<<g.reduce, CL_T, accb, s>>>(w, sk, ix, spare, passes); break;
-    case 2: k_collapse<2><<<g.reduce, CL_T, accb, s>>>(w, sk, ix, spare, passes); break;
-    case 4: k_collapse<4><<<g.reduce, CL_T, accb, s>>>(w, sk, ix, spare, passes); break;
-    case 8: k_collapse<8><<<g.reduce, CL_T, accb, s>>>(w, sk, ix, spare, passes); break;
+    case 1: launch(std::integral_constant<int, 1>()); break;
+    case 2: launch(std::integral_constant<int, 2>()); break;
+    case 4: launch(std::integral_constant<int, 4>()); break;
+    case 8: launch(std::integral_constant<int, 8>()); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -704,7 +792,7 @@ hipError_t enqueue_collapse(const Work &w, const Grids &g, int passes, hipStream
 int collapse_occupancy()
 {
     int nb = 1;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_collapse<2>, CL_T, 0) != hipSuccess) nb = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_collapse<2, false>, CL_T, 0) != hipSuccess) nb = 1;
     return nb < 1 ? 1 : nb;
 }
 

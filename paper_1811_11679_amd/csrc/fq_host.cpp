@@ -587,6 +587,10 @@ Grids sized_grids(const fq_ctx *c, double room)
     // (about as many cluster selections as attempts; a block stages the prefix for a few passes)
     g.ccmc = fit(c->grids.ccmc, c->att_hint, 4 * 256);
     g.ss = c->ss_active ? 1 : 0;
+    // Where the mean determinant fills half a window the larger ones overrun it (kept
+    // down to a third): the ring of six at 6e5 records on 400 determinants 288 us an
+    // iteration with the other kernel, 272; of seven at 3.5e5 on 1225 203 and 221.
+    g.heavy = c->repeat > (c->plan.heavy ? 340.0 : 512.0) ? 1 : 0;
     return g;
 }
 
@@ -642,7 +646,7 @@ void choose_plan(fq_ctx *c)
     const Grids lo = sized_grids(c, 1.0), hi = sized_grids(c, 8.0);
     auto within = [](int x, int a, int b) { return x >= a && x <= b; };
     const Grids &g = c->plan;
-    const bool keep = !ended && p == c->w.sort_p && g.ss == lo.ss && within(g.part, lo.part, hi.part) &&
+    const bool keep = !ended && p == c->w.sort_p && g.ss == lo.ss && g.heavy == lo.heavy && within(g.part, lo.part, hi.part) &&
                       within(g.spawn, lo.spawn, hi.spawn) && within(g.sort, lo.sort, hi.sort) &&
                       within(g.reduce, lo.reduce, hi.reduce) && within(g.merge, lo.merge, hi.merge) &&
                       within(g.newdiag, lo.newdiag, hi.newdiag) && within(g.ccmc, lo.ccmc, hi.ccmc) && g.spawn_i == lo.spawn_i &&

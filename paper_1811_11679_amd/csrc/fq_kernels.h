@@ -239,6 +239,7 @@ struct Grids {
     // radix-sort keys per thread (8, 12, 16)
     int spawn_i = 4, merge_i = 4, sort_i = 12;
     int ccmc = 1024;  // blocks of the cluster-sampling kernel
+    int heavy = 0;    // many spawned records per determinant
     int ss = 0;       // the deterministic space is active
     int diag_chunk = 16384;  // flags a block of the new-determinant diagonal kernel scans at once
 };

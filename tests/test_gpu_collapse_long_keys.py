@@ -70,3 +70,29 @@ def test_growth_beyond_the_plan(ecut, tau, walkers, bits):
     say(f"[case] {ctx.W} words, {bits} bits: {records} records in 256 groups")
     assert records / 256 > 128
     ctx.close()
+
+
+# More than 512 records per determinant from the first iteration on: the kernel that
+# keeps several records of a group in flight, on groups of one determinant and, with
+# few hash bits, of several
+@pytest.mark.parametrize("ecut,walkers,tau", [(3, 1e5, 0.02), (5, 1e5, 0.05), (9, 2e5, 0.05), (14, 3e5, 0.05)])
+@pytest.mark.parametrize("bits", [64, 12, 5])
+def test_many_records_per_determinant(ecut, walkers, tau, bits):
+    n = 1 if bits == 64 else 2
+    sysd = dict(kind="ueg", rs=1.0, ecut_n2=ecut, n_alpha=1, n_beta=1)
+    q = dict(workloads.UEG14["qmc"], tau=tau, init_pop=walkers, target_population=1e12, initiator=0)
+    ctx = gpu_context([sysd] * n, [q] * n, replicas=list(range(n)), main_capacity=1 << 14, spawn_capacity=1 << 22)
+    if bits < 64:
+        ctx.set_sort_key_bits(bits)
+    runs = [O.Run(oracle_system(sysd), oracle_qmc(sysd, q, replica=r)) for r in range(n)]
+    for it in range(3):
+        ctx.step(1)
+        for r, run in enumerate(runs):
+            run.step(1)
+            where = f"cutoff {ecut}, {bits} bits, instance {r}, iteration {it}"
+            assert_same_lists(ctx, run, instance=r, where=where)
+            e = ctx.estimators(r)
+            assert_same_estimators(e, run.estimators(), where=where)
+            assert e["n_spawned"] > 512 * e["n_spawn_events"]
+    say(f"[case] {ctx.W} words, {bits} bits: {e['n_spawned']} records on {e['n_spawn_events']} determinants")
+    ctx.close()

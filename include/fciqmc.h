@@ -292,7 +292,8 @@ fq_status fq_import_walkers(fq_ctx *ctx, int32_t instance, const uint64_t *keys,
 fq_status fq_shift_state(const fq_ctx *ctx, int32_t instance, double *shift, int64_t *n_prev,
                          int32_t *vary_shift);
 
-/* Spawned walkers of the last iteration of one instance (unordered):
+/* Spawned walkers of the last iteration of one instance, or of the one that a
+ * step failed in if it failed after they were sorted, none if before (unordered):
  * keys[i*W + w], amps[i] (units), init[i] (1 if the parent was an initiator). */
 fq_status fq_export_spawns(const fq_ctx *ctx, int32_t instance, uint64_t *keys, int32_t *amps,
                            uint8_t *init, int64_t cap, int64_t *n_out);

@@ -1540,6 +1540,8 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
             fix.err = 0;
             fix.t = (uint32_t)(tf - 1);
             fix.n_main_new = ctl.n_main;
+            // records that were not sorted have no index: none are left to export
+            if (err & (ERR_SPAWN_CAP | ERR_OVERFLOW | ERR_NOREF)) fix.n_spawn = 0;
             HIPCHK(c, h2d(c->stream, c->w.ctl, &fix, sizeof(Ctl)));
             // the failing merge may have written attempt offsets and deterministic
             // positions for a list that is discarded: rebuild them for the restored one

@@ -43,6 +43,27 @@ def test_list_capacities(main, spawn, graph):
     ctx.close()
 
 
+@pytest.mark.parametrize("main,spawn,sorted_", [(1 << 18, 6000, False), (1 << 15, 1 << 17, True)])
+def test_spawns_of_a_failed_iteration(main, spawn, sorted_):
+    """Records are exported by the index the sort makes: an iteration that fails
+    before it has none, one that fails in the merge has them all."""
+    sysd, w = workloads.UEG14["system"], workloads.UEG14["qmc"]
+    q = dict(w, init_pop=5e3, target_population=2e4)
+    say(f"[case] spawns after a failed step, capacities {main} and {spawn}")
+    ctx = gpu_context([sysd], [q], main_capacity=main, spawn_capacity=spawn)
+    at = _fails(ctx, F.FQ_ECAPACITY, times=1)
+    keys, amps, init = ctx.spawns()
+    if sorted_:
+        run = O.Run(oracle_system(sysd), oracle_qmc(sysd, q))
+        run.step(at + 1)
+        want = run.spawns()
+        rows = [sorted(zip(map(tuple, k.tolist()), a.tolist(), i.tolist())) for k, a, i in ((keys, amps, init), want)]
+        assert rows[0] == rows[1] and len(rows[0]) > 1000
+    else:
+        assert len(amps) == 0
+    ctx.close()
+
+
 def test_cluster_records_beyond_the_spawn_capacity():
     s, q = workloads.UEG14_CCSD["system"], dict(workloads.UEG14_CCSD["qmc"], init_pop=2e4, target_population=1e9)
     say("[case] CCSD on the 14-electron gas, room for half of the clusters' records")

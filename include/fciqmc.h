@@ -346,7 +346,7 @@ fq_status fq_set_graph(fq_ctx *ctx, int32_t on);
  * ordered). Only the top `bits` (1..64) bits of each determinant's 64-bit hash
  * then enter its sort key, so that many determinants share a sort key and
  * ties are broken by the determinant itself, in the main list and in the
- * spawned list (collision fix-up and repeated reduction every iteration).
+ * spawned list.
  * Results are unchanged: the random streams are keyed by the full hash.
  * Needs two or more instances (FQ_EINVAL otherwise: a single instance's
  * kernels use the sort key as the hash) and must precede the deterministic

@@ -232,7 +232,7 @@ struct Layout {
     size_t ctl, acc, hist, shift, rep, sys, tables, att, span, mpart, mtile, mrun, mpop, msrc, st_scan, st_sort;
     size_t part_red, part_mrg, newdet;
     size_t main[2][5];
-    size_t sp[7];
+    size_t sp[5];
     size_t u[4];
     size_t ds[14];
     size_t dkeys;
@@ -307,11 +307,9 @@ Layout make_layout(int R, int W, int64_t mcap, int64_t scap, int64_t tables, int
     }
     L.sp[0] = take(8 * (size_t)scap);
     L.sp[1] = take(8 * (size_t)scap * (W + 1));
-    L.sp[2] = take(0);
-    L.sp[3] = take(0);
-    L.sp[4] = take(8 * (size_t)scap);
-    L.sp[5] = take(4 * (size_t)scap);
-    L.sp[6] = take(4 * (size_t)scap);
+    L.sp[2] = take(8 * (size_t)scap);
+    L.sp[3] = take(4 * (size_t)scap);
+    L.sp[4] = take(4 * (size_t)scap);
     L.u[0] = take(8 * (size_t)scap);
     L.u[1] = take(8 * (size_t)scap * W);
     L.u[2] = take(8 * (size_t)scap);
@@ -1105,9 +1103,9 @@ fq_status init_system(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc, con
     w.part_mrg = (long long *)(c->ws + c->L.part_mrg);
     w.sp.skey = (uint64_t *)(c->ws + c->L.sp[0]);
     w.sp.rec = (uint64_t *)(c->ws + c->L.sp[1]);
-    w.sp.skey2 = (uint64_t *)(c->ws + c->L.sp[4]);
-    w.sp.idx = (uint32_t *)(c->ws + c->L.sp[5]);
-    w.sp.idx2 = (uint32_t *)(c->ws + c->L.sp[6]);
+    w.sp.skey2 = (uint64_t *)(c->ws + c->L.sp[2]);
+    w.sp.idx = (uint32_t *)(c->ws + c->L.sp[3]);
+    w.sp.idx2 = (uint32_t *)(c->ws + c->L.sp[4]);
     w.u.skey = (uint64_t *)(c->ws + c->L.u[0]);
     w.u.key = (uint64_t *)(c->ws + c->L.u[1]);
     w.u.sum = (long long *)(c->ws + c->L.u[2]);

@@ -26,14 +26,13 @@ enum : uint32_t {
     ERR_MAIN_CAP = 2u,
     ERR_OVERFLOW = 4u,
     ERR_ATTEMPTS = 8u,
-    ERR_UNIQ_CAP = 16u,
     ERR_COLLISION = 32u,
     ERR_NOREF = 64u,  // CCMC: the reference holds no walkers (cluster weights divide by N_0)
 };
 
 enum : int {
     TK_SCAN = 0,
-    TK_SORT = 1,   // 8 passes: 1..8
+    TK_SORT = 1,   // one per digit of the sort key: 1..8
     TK_SPAWN = 12,
     TK_CCMC = 13,
     TK_COUNT = 16,
@@ -45,12 +44,9 @@ struct Ctl {
     long long n_att;       // total spawning attempts this iteration
     long long n_att_new;   // attempts of the list the merge has just written
     unsigned long long n_spawn;  // spawned walkers written
-    long long pad_uniq;
     uint32_t t;            // iteration counter (1 = first iteration)
     uint32_t err;
-    uint32_t pad_coll;
     uint32_t ss_active;
-    uint32_t pad_ts;
     uint32_t tickets[TK_COUNT];
     uint32_t hist[8][256];  // radix-sort digit histogram of the spawned keys
     // CCMC: N_0 and the sum of |N_i| over the excitors at the start of the
@@ -58,7 +54,6 @@ struct Ctl {
     long long ccmc_n0;
     long long ccmc_nex;
     uint32_t n_single;
-    uint32_t pad_ccmc;
 };
 
 // Per-replica estimator accumulators (exact integers).
@@ -206,7 +201,6 @@ struct Work {
     long long att_cap;  // attempts of an iteration the partition takes
     int32_t R, rb, W, hist_len;
     int32_t sort_p;  // radix passes over the top digits of the sort keys (1..SORT_P_MAX)
-    int32_t pad_sort;
     uint64_t hmask;  // hash bits that enter a sort key (all but in collision tests)
     int32_t tau_search;  // track the maxima of the time-step search (per replica)
     int32_t lds_tables;  // bytes of UEG tables the spawn kernel stages in LDS (0: read from global)

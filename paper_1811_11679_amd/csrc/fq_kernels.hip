@@ -1,10 +1,10 @@
-// Kernels of one FCIQMC projector iteration (paper Sec. 2.1 eq. fciqmc,
-// Sec. 2.4 spawning / death / annihilation, appendix "Parallelization":
-// sorted main list, spawned list sorted and merged into it), written for
-// gfx950: 64-wide wavefronts, LDS-staged tiles, persistent grids that read
-// their problem sizes from device memory, decoupled look-back for every
-// prefix that crosses tiles (Merrill & Garland 2016) and a onesweep LSD
-// radix sort (Adinets & Merrill 2022).
+// One FCIQMC projector iteration (paper Sec. 2.1 eq. fciqmc, Sec. 2.4 spawning /
+// death / annihilation, appendix "Parallelization": sorted main list, spawned list
+// sorted and merged into it) enqueued on a stream, its radix passes, the
+// deterministic projection and the set-up kernels, for gfx950: 64-wide
+// wavefronts, LDS-staged tiles, grids that read their problem sizes from device
+// memory and a onesweep LSD radix sort (Adinets & Merrill 2022) with decoupled
+// look-back (Merrill & Garland 2016).
 #include "fq_kernels.h"
 #include "fq_scan.h"
 

@@ -126,7 +126,7 @@ struct MergeCfg {
     static constexpr int WPE = MI >= 4 || W > 2 ? 4 : (MI == 2 ? 5 : 6);  // waves per SIMD
 };
 static_assert(MergeCfg<1, 1>::TILE >= MERGE_TILE_MIN && MergeCfg<8, 2>::TILE >= MERGE_TILE_MIN,
-              "the merge partition and status arrays are sized for MERGE_TILE_MIN-position tiles");
+              "the splits and totals of the merge are sized for MERGE_TILE_MIN-position tiles");
 
 template <int W>
 __device__ __forceinline__ void load_key(const uint64_t *base, long long cap, long long i, uint64_t (&k)[W])

@@ -8,8 +8,8 @@ namespace fq {
 // ---------------------------------------------------------------------------
 // spawning (Sec. 2.4): one thread per attempt, parents found through the
 // attempt prefix (load balanced: a heavily populated determinant spreads its
-// attempts over many threads and tiles). A tile of 1024 consecutive attempts
-// finds its spawn count, reserves that many records with one atomic on the
+// attempts over many threads and tiles). A tile of consecutive attempts, SP_I for
+// each of its threads, finds its spawn count, reserves that many records with one atomic on the
 // spawn counter and writes them contiguously. The records of different tiles
 // land in completion order: the radix sort and the segmented sums downstream
 // make the result independent of it (equal keys are summed as exact
@@ -153,8 +153,9 @@ __global__ __launch_bounds__(SP_T) void k_spawn(Work w)
         uint8_t init[SP_I];
         uint32_t rep[SP_I];
         // phase 1: the parent of each attempt (blocked: thread t takes attempts
-        // 4t .. 4t+3 of the tile; one search finds the first parent, later
-        // attempts advance from it), its first attempt and its attempt count
+        // SP_I t to SP_I t + SP_I - 1 of the tile; one search finds the first
+        // parent, later attempts advance from it), its first attempt and its
+        // attempt count
         long long pi[SP_I], pa0[SP_I], pnat[SP_I];
         {
             long long ip = -1;

@@ -241,7 +241,7 @@ fq_status fq_init_system(fq_ctx **out, const fq_system *sys, const fq_qmc *qmc,
  * without d_workspace / ws_bytes; the array of the current device is used.
  * Errors: FQ_ECAPACITY (nothing created) when fq_workspace_bytes() of the
  * arguments exceeds FQ_STATIC_WORKSPACE_BYTES (a few 1e4 determinants: the
- * 8-site Hubbard ring with 16384 determinants and 65536 spawns needs 7.3 MiB);
+ * 8-site Hubbard ring with 16384 determinants and 65536 spawns needs 7.9 MiB);
  * FQ_ESTATE when a context made by this call on the same device has not yet
  * been destroyed (every such context would share the one array, and calls on
  * two of them would race, so only one may live per device); FQ_EINVAL as for

@@ -114,8 +114,8 @@ __device__ void acc_terms(long long *tab, int rl, EstAcc *g, int rep, int32_t n0
 // decoupled look-back moved 65 bytes per entry instead of 101 but took 2890 us
 // for 6e7 entries: its time fitted 8.6 ns per tile + 2310 us, a tile being held
 // up by every tile in flight before it, and wider look-back reads made it
-// slower, 3650 us. Now k_merge 1500 us, 45% of it vector ALU, the rest the
-// latency of loads, bisection and rounding; k_move 1150 us, 5.0 TB/s.)
+// slower, 3650 us. Now k_merge 1480 us, 2.2 TB/s and 44% of it vector ALU, the
+// rest the latency of loads, bisection and rounding; k_move 1160 us, 4.1 TB/s.)
 // ---------------------------------------------------------------------------
 // MI: merge positions per thread and tile, 1, 2 or 4 for keys of up to two
 // words (chosen per context), 2 for longer keys

@@ -204,8 +204,9 @@ typedef struct {
                                  of the last checked iteration (0 if none) */
     double ss_error_bound;    /* a priori bound of that ratio for the BF16 x3 / FP32 scheme */
     double tau;               /* time step of the next iteration (tau_search may lower it) */
-    double spawn_ratio_max;   /* tau_search: largest |H_ji| / p_gen of any attempt so far, as of
-                                 the end of the fq_step call (0 without tau_search) */
+    double spawn_ratio_max;   /* tau_search: largest |H_ji| / p_gen of any attempt up to the next
+                                 shift update, or to the end of the fq_step call if that is
+                                 earlier (0 without tau_search) */
     int64_t pair_limbs[4];    /* CCMC: exact fixed-point (2^-64) sum over pairs of singles a < b
                                  of H_0,ab sgn(a_a a_b D_0) N_a N_b (units^2); proj_numerator and
                                  proj_energy add it divided by N_0. Zero otherwise. */

@@ -1426,7 +1426,16 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
     constexpr int NE = N_KERNEL_SLOTS + 1;
     std::vector<hipEvent_t> evs;
     int done = 0;
-    int64_t whole = c->t;  // end of the iterations up to the next decision point
+    int64_t whole0 = c->t, whole = c->t;  // the iterations up to the next decision point
+    // the records of those iterations report one maximum of the time-step search, the
+    // last, also where they were enqueued in several parts
+    auto report_ratio = [&](int64_t to) {
+        for (int r = 0; r < c->R; ++r) {
+            std::vector<fq_estimators_t> &h = c->hist[r];
+            for (size_t i = h.size() - std::min<size_t>(h.size(), (size_t)(to - whole0)); i < h.size(); ++i)
+                h[i].spawn_ratio_max = c->rs_max[r];
+        }
+    };
     while (done < n_iterations) {
         // CCMC: the prefix of |N_i| travels in look-back words of 38 bits; the
         // iterations up to a decision point start only with room for their growth
@@ -1449,6 +1458,7 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
             if (c->L.single_key > c->L.st_ccmc)
                 HIPCHK(c, fill0(c->stream, c->ws + c->L.st_ccmc, c->L.single_key - c->L.st_ccmc));
         }
+        if (c->t >= whole) whole0 = c->t;
         whole = stop;
         stop = c->t + expect_sizes(c, (int)(stop - c->t));
         choose_plan(c);
@@ -1571,6 +1581,7 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
                     c->last[r] = e;
                 }
             c->t = tf - 1;
+            report_ratio(c->t);
             if (err & (ERR_OVERFLOW | ERR_ATTEMPTS)) return fail(c, FQ_EOVERFLOW, "population or spawn exceeds the fixed-point range");
             if (err & ERR_COLLISION) return fail(c, FQ_ESTATE, "more than 64 spawned determinants share one sort key (not a hash collision)");
             if (err & ERR_NOREF) return fail(c, FQ_ENOREF, "CCMC: the reference determinant holds no walkers");
@@ -1639,6 +1650,7 @@ fq_status fq_step(fq_ctx *c, int32_t n_iterations)
         }
         if (c->recent.size() > 32) c->recent.erase(c->recent.begin(), c->recent.end() - 16);
         c->t = stop;
+        report_ratio(stop);
         done += nb;
         for (int r = 0; r < c->R; ++r) c->h_shift[r] = c->shift[r];
         HIPCHK(c, hipMemcpyAsync(c->w.shift, c->h_shift, 8 * c->R, hipMemcpyHostToDevice, c->stream));

@@ -136,3 +136,27 @@ def test_attempts_of_small_capacities(kind, items, most):
             assert ctx.estimators()["n_spawned"] > 0
             assert_same_lists(ctx, run, where=f"{attempts} attempts")
         ctx.close()
+
+
+@pytest.mark.parametrize("steps", [(10,), (7, 13), (25,)])
+def test_records_between_two_shift_updates_report_one_ratio(steps):
+    """However a call's iterations are enqueued, those up to the next shift update (or the
+    end of the call) report the largest ratio of all of them."""
+    ints = synth.molecular_integrals(20)
+    sysd = dict(kind="molecular", n_alpha=3, n_beta=5)
+    q = dict(workloads.MOL30["qmc"], tau=0.002, init_pop=50.0, target_population=1e4, tau_search=1)
+    say(f"[case] time-step search, calls of {steps}")
+    ctx = gpu_context([sysd], [q], ints=ints, main_capacity=1 << 18, spawn_capacity=1 << 18)
+    run = O.Run(oracle_system(sysd, ints), oracle_qmc(sysd, q))
+    for n in steps:
+        ctx.step(n)
+        first = ctx.estimators()["iteration"] - n
+        own = []
+        for _ in range(n):
+            run.step(1)
+            own.append(run.estimators()["spawn_ratio_max"])
+        got = [e["spawn_ratio_max"] for e in ctx.history()]
+        ends = [min((first + i) // 10 * 10 + 10, first + n) - first for i in range(n)]
+        assert got == [own[e - 1] for e in ends]
+        assert len(set(own)) > 1 or first > 0
+    ctx.close()

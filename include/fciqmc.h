@@ -337,7 +337,8 @@ fq_status fq_iteration_times(const fq_ctx *ctx, double *ms, int64_t cap, int64_t
 
 /* Graph replay: with on = 1, every block of shift_period iterations between
  * two host shift updates is captured once into a HIP graph (per main-list
- * parity) and replayed with one launch. The stream given to fq_init_system
+ * parity) and replayed with one launch; while the list grows, and in the block
+ * after a list has been put in place, kernels are launched one by one. The stream given to fq_init_system
  * must not be the legacy default stream. Timing (fq_set_timing) launches
  * kernels one by one and takes precedence. */
 fq_status fq_set_graph(fq_ctx *ctx, int32_t on);
